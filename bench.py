@@ -26,6 +26,8 @@ METRIC = "MERA energy+gradient evals/s at chi=24 (TFLOP/s, % peak); job p50/p99 
 # Dense MFMA peaks in the flops the library counts (2 per multiply-add of the contraction). The split-bf16 form
 # spends three bf16 products on each multiply-add, so its ceiling is a third of the 2.5 PFLOP/s bf16 peak.
 PEAK_TFLOPS = {"fp32": 157.3, "fp64": 78.6, "bf16x3": 2500.0 / 3}
+# The FP32 form's split kernels (variants marked s3) form a multiply-add from six bf16 products.
+PEAK_SPLIT_FP32 = 2500.0 / 6
 
 
 def parse():
@@ -121,20 +123,21 @@ def cpu_baseline(a, sample_chi, sample_T, flops_sample, flops_bench):
 
 
 def counter_traffic(kernel_variant):
-    """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter summary, or None when the
-    kernel source changed since the counters were taken or the summary covers another variant."""
+    """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter summaries, or None when the
+    kernel's source changed since the counters were taken or no summary covers the variant."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", "gett_f32_chi24_counters.md")
-    src = os.path.join(ROOT, "paper_2007_03638_amd", "csrc", "gett.hip")
-    if not os.path.exists(path):
-        return None
-    sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    fields = dict(l.split(": ", 1) for l in open(path).read().splitlines() if ": " in l and not l.startswith("|"))
-    if fields.get("gett_source_sha256_prefix", "").strip() != sha:
-        return None
-    if fields.get("kernel_variant", "").strip() != kernel_variant:
-        return None
-    return float(fields["traffic_bytes_per_launch"])
+    for summary, source in (("gett_f32_chi24_counters.md", "gett.hip"), ("gett_split_chi24_counters.md", "gett_split.hip")):
+        path = os.path.join(ROOT, "profiles", summary)
+        src = os.path.join(ROOT, "paper_2007_03638_amd", "csrc", source)
+        if not os.path.exists(path):
+            continue
+        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+        fields = dict(l.split(": ", 1) for l in open(path).read().splitlines() if ": " in l and not l.startswith("|"))
+        if fields.get("gett_source_sha256_prefix", "").strip() != sha:
+            continue
+        if fields.get("kernel_variant", "").strip() == kernel_variant:
+            return float(fields["traffic_bytes_per_launch"])
+    return None
 
 
 def precision_check(a, ctx, opt, h3):
@@ -230,7 +233,7 @@ def run_eval_bench(a):
     top = stats[0]
     achieved = top["flops"] / top["seconds"] / 1e12
     gemm_time = sum(s["seconds"] for s in stats)
-    peak = PEAK_TFLOPS[a.prec]
+    peak = PEAK_SPLIT_FP32 if ",s3" in top["kernel"] else PEAK_TFLOPS[a.prec]
     out = {
         "metric": METRIC,
         "value": evals / dt,

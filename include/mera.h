@@ -44,7 +44,10 @@ typedef enum {
 } mera_status;
 
 /* Arithmetic of the bulk contractions. FP64: double-precision MFMA throughout. FP32: single-precision
- * MFMA with single-precision accumulation, double-precision dot products, traces and Krylov scalars.
+ * operands and accumulation, double-precision dot products, traces and Krylov scalars; large contractions run on the
+ * bf16 MFMA units with each operand split into three bf16 parts (exact: 24 mantissa bits) and the six leading
+ * products of the parts, whose error against FP64 is below that of the single-precision MFMA; a non-finite operand
+ * element gives there what single-precision multiply-adds give.
  * BF16X3: each FP32 operand split into bf16 hi + lo parts, products hi*hi + hi*lo + lo*hi on the bf16
  * MFMA units with FP32 accumulation. */
 typedef enum { MERA_FP64 = 0, MERA_FP32 = 1, MERA_BF16X3 = 2 } mera_prec;

@@ -1,7 +1,7 @@
 // Permute-fused GETT kernels for gfx950: LDS-staged, register-prefetched tile loads (16-byte vectors where the
 // layouts allow; row offsets from tables, k offsets computed from the contracted legs), MFMA inner products
 // (f32 32x32x2, f64 16x16x4, bf16 16x16x32 for the split-bf16 form), split-K partials reduced in FP64.
-#include "gett.h"
+#include "gett_device.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -10,23 +10,7 @@ namespace mera {
 
 namespace {
 
-// One launch runs the same contraction (same tables and extents) for up to kGettMaxGroup independent operand
-// sets; blockIdx.y selects the set.
-struct Args {
-  const void* A[kGettMaxGroup];
-  const void* B[kGettMaxGroup];
-  void* C[kGettMaxGroup];
-  void* partial[kGettMaxGroup];  // splits x M x N partial sums per set (accumulator type); used when split != 0
-  const int64_t* a_m;
-  const int64_t* b_n;
-  const int64_t* c_m;
-  const int64_t* c_n;
-  GettKLegs kl;
-  int64_t M, N, K;
-  int64_t kchunk;  // K range per split, a multiple of BK
-  double alpha, beta;
-  int split;       // 1: write partial sums, 0: write C
-};
+using Args = GettArgs;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -59,21 +43,6 @@ template <> struct Mma<double> {
   __device__ static inline int row(int lane, int i) { return (lane >> 4) + 4 * i; }
   __device__ static inline int col(int lane) { return lane & 15; }
 };
-
-// Offset of the k-th index along the contracted legs (fastest leg first; see GettKLegs): NKL digit extractions
-// by reciprocal multiplication, no memory access. Entries past kl.n are zero and contribute nothing.
-template <int NKL>
-__device__ inline uint64_t k_offset(uint32_t k, const GettKLegs& kl, const uint32_t* stride) {
-  uint64_t off = 0;
-  uint32_t q = k;
-#pragma unroll
-  for (int l = 0; l + 1 < NKL; ++l) {
-    const uint32_t qn = __umulhi(q, kl.mag[l]);
-    off += (uint64_t)(q - qn * kl.ext[l]) * stride[l];
-    q = qn;
-  }
-  return off + (uint64_t)q * stride[NKL - 1];
-}
 
 // Tile loader: BMN x BK tile of an operand whose element (r, k) lives at base + off_r[r] + k_offset(k).
 // KFAST: consecutive threads walk k (the operand's unit-stride leg is a K leg); each thread then owns one k
@@ -196,32 +165,6 @@ struct VecLoader {
     else store<LD, true>(lds, kt, kend);
   }
 };
-
-// Workgroups are dispatched to the 8 XCDs round-robin (workgroup b runs on XCD b % 8). Remap so that each
-// XCD processes a contiguous range of logical tiles: consecutive tiles share an A panel, which then stays in
-// that XCD's L2 instead of being fetched by all eight. The tail (ntiles % 8 tiles) keeps the identity map.
-__device__ inline int64_t xcd_tile(int64_t b, int64_t ntiles) {
-  const int64_t full = ntiles / 8;
-  return (b < full * 8) ? (b % 8) * full + b / 8 : b;
-}
-
-// Origin of logical tile `tile`. Tiles are taken in groups of kTileGroup panels of the dimension with more tiles
-// (the larger operand); within a group that dimension runs fastest, then the other one. The 64 tiles an XCD runs
-// at once then cover about 8 panels of each operand, which its L2 serves to all of them: each operand is fetched
-// from beyond L2 about (tiles of the other dimension) / kTileGroup times instead of once per tile of the other
-// dimension for the smaller operand.
-constexpr int64_t kTileGroup = 8;
-template <int BM, int BN>
-__device__ inline void tile_origin(int64_t tile, int64_t M, int64_t N, int64_t& m0, int64_t& n0) {
-  const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-  const bool mgroups = tm >= tn;
-  const int64_t tbig = mgroups ? tm : tn, tsmall = mgroups ? tn : tm;
-  const int64_t grp = tile / (kTileGroup * tsmall), loc = tile % (kTileGroup * tsmall);
-  const int64_t gsize = (tbig - grp * kTileGroup < kTileGroup) ? tbig - grp * kTileGroup : kTileGroup;
-  const int64_t big = grp * kTileGroup + loc % gsize, small = loc / gsize;
-  m0 = (mgroups ? big : small) * BM;
-  n0 = (mgroups ? small : big) * BN;
-}
 
 template <typename T, int BM, int BN, int BK, bool AKF, bool BKF, int NKL, bool VEC>
 // At most 256 registers per lane (2 waves per SIMD) for every tile; the register allocator then keeps the
@@ -402,27 +345,15 @@ __global__ void __launch_bounds__(256, 2) gett_kernel(Args g) {
   }
 }
 
-// ---- split-bf16 (hi + lo) form: C ~= A_hi B_hi + A_hi B_lo + A_lo B_hi on the bf16 MFMA ------------------
+// ---- split-bf16 (hi + lo) form with scalar loads: C ~= A_hi B_hi + A_hi B_lo + A_lo B_hi on the bf16 MFMA (operands
+// that allow 16-byte loads run on gett_split.hip where both extents reach 128) -----------------------------------
 
 __device__ inline void split_bf16(float x, __bf16& hi, __bf16& lo) {
   hi = (__bf16)x;
   lo = (__bf16)(x - (float)hi);
 }
 
-// The same split for two elements: one packed conversion gives both hi values, whose FP32 values are the packed
-// word's halves moved to the top 16 bits (the subtraction is exact), then one packed conversion of the two lo.
-// The empty asm statement (no instruction) hides the packed word's origin from the optimiser, which would
-// otherwise convert x0 a second time to rebuild its FP32 hi.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ inline void split_bf16x2(float x0, float x1, bf16x2& hi, bf16x2& lo) {
-  uint32_t hb = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)x0, (__bf16)x1});
-  __asm__("" : "+v"(hb));
-  hi = __builtin_bit_cast(bf16x2, hb);
-  const float h0 = __uint_as_float(hb << 16), h1 = __uint_as_float(hb & 0xffff0000u);
-  lo = bf16x2{(__bf16)(x0 - h0), (__bf16)(x1 - h1)};
-}
-
-// Epilogue of the split-bf16 kernels: 16 x 16 accumulator blocks (acc[i] -> row 4 (lane / 16) + i, col lane % 16),
+// Epilogue of the split-bf16 kernel: 16 x 16 accumulator blocks (acc[i] -> row 4 (lane / 16) + i, col lane % 16),
 // written as split-K partials or as C = alpha acc + beta C through the C offset tables.
 template <int FM, int FN>
 __device__ inline void bf16x3_epilogue(const Args& g, const f32x4 (&acc)[FM][FN], int64_t m0, int64_t n0, int wm,
@@ -570,161 +501,6 @@ __global__ void __launch_bounds__(256) gett_bf16x3_kernel(Args g) {
   bf16x3_epilogue<FM, FN>(g, acc, m0, n0, wm, wn, lane, grp);
 }
 
-// Split-bf16 form with 16-byte tile loads (both operands' layouts allow them): 128 x 128 tiles, BK = 32, each
-// thread loading four 4-element vectors per operand and tile. Thread t owns rows 4 (t / 8) .. 4 (t / 8) + 3 and
-// k 4 (t % 8) .. 4 (t % 8) + 3 of the tile. A k-walking operand's vector is 4 consecutive k of one row; a
-// row-walking operand's four vectors are the same 4 rows at 4 consecutive k, transposed in registers. Either way a
-// thread stages 4 k of a row at a time: split into hi and lo and written as one 8-byte LDS store per plane (planes
-// row-major with k contiguous, pitch BK + 8, as in the kernel above). Eight consecutive lanes fill 64 contiguous
-// bytes of one row and the next eight lanes start 4 rows (80 dwords) further, so the stores of 32 lanes cover 64
-// distinct banks; with the older assignment (a row-walking thread on rows 4 (t % 32) ..) 32 lanes wrote 4 rows
-// apart at one k, all into 4 bank pairs, and the kernel spent over a third of its wave cycles waiting on LDS.
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-template <bool KFAST, int NKL>
-struct Bf16VecLoader {
-  static constexpr int BMN = 128, BK = 32, LDK = BK + 8;
-  const float* rowp[4];
-  int r0, k0;
-  f32x4 reg[4];
-
-  __device__ inline void init(const float* base, const int64_t* off_r, int64_t rbase, int tid) {
-    r0 = 4 * (tid / 8);  // rows r0 .. r0 + 3
-    k0 = 4 * (tid % 8);
-    if (KFAST) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) rowp[i] = base + off_r[rbase + r0 + i];
-    } else {
-      rowp[0] = base + off_r[rbase + r0];
-    }
-  }
-  // The fastest contracted leg's extent is a multiple of 4 (required by the launch), and kt + k0 is one too, so
-  // the thread's 4 k's differ only in that leg's digit: one offset, then steps of that leg's stride.
-  __device__ inline void load(int64_t kt, int64_t K, const GettKLegs& kl, const uint32_t* stride) {
-    const uint32_t k = (uint32_t)kt + (uint32_t)k0, klast = (uint32_t)K - 4;
-    const uint64_t o = k_offset<NKL>(k < klast ? k : klast, kl, stride);
-    if (KFAST) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) reg[i] = *reinterpret_cast<const f32x4*>(rowp[i] + o);
-    } else {
-      const float* p = rowp[0] + o;
-      const uint64_t s0 = stride[0];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) reg[j] = *reinterpret_cast<const f32x4*>(p + j * s0);
-    }
-  }
-  // stages the tile starting at kt; KMASK: zero past kend
-  template <bool KMASK>
-  __device__ inline void store(__bf16* hi, __bf16* lo, int64_t kt, int64_t kend) const {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float x[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        x[j] = KFAST ? reg[i][j] : reg[j][i];
-        if (KMASK && kt + k0 + j >= kend) x[j] = 0.f;
-      }
-      bf16x2 h01, l01, h23, l23;
-      split_bf16x2(x[0], x[1], h01, l01);
-      split_bf16x2(x[2], x[3], h23, l23);
-      const bf16x4 h{h01[0], h01[1], h23[0], h23[1]}, l{l01[0], l01[1], l23[0], l23[1]};
-      const int row = r0 + i;
-      *reinterpret_cast<bf16x4*>(&hi[row * LDK + k0]) = h;
-      *reinterpret_cast<bf16x4*>(&lo[row * LDK + k0]) = l;
-    }
-  }
-  __device__ inline void store_tile(__bf16* hi, __bf16* lo, int64_t kt, int64_t kend) const {
-    if (kt + BK <= kend) store<false>(hi, lo, kt, kend);
-    else store<true>(hi, lo, kt, kend);
-  }
-};
-
-// Pipeline as in gett_kernel: double-buffered planes, tile t+1 staged from registers at the start of tile t and
-// tile t+2 loaded right after (fenced), one barrier per tile; one MFMA k-step (k = 32) per tile.
-template <bool AKF, bool BKF, int NKL>
-__global__ void __launch_bounds__(256, 2) gett_bf16x3_vec_kernel(Args g) {
-  constexpr int BM = 128, BN = 128, BK = 32, LDK = BK + 8;
-  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 16, FN = WN / 16;
-  __shared__ __attribute__((aligned(16))) __bf16 Ah[2][BM * LDK];
-  __shared__ __attribute__((aligned(16))) __bf16 Al[2][BM * LDK];
-  __shared__ __attribute__((aligned(16))) __bf16 Bh[2][BN * LDK];
-  __shared__ __attribute__((aligned(16))) __bf16 Bl[2][BN * LDK];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = (wave >> 1) * WM;
-  const int wn = (wave & 1) * WN;
-  int64_t m0, n0;
-  tile_origin<BM, BN>(xcd_tile(blockIdx.x, gridDim.x), g.M, g.N, m0, n0);
-  const int64_t kb = (int64_t)blockIdx.z * g.kchunk;
-  const int64_t ke = (g.K < kb + g.kchunk) ? g.K : kb + g.kchunk;
-  const int grp = blockIdx.y;
-  const float* __restrict__ A = static_cast<const float*>(g.A[grp]);
-  const float* __restrict__ B = static_cast<const float*>(g.B[grp]);
-
-  Bf16VecLoader<AKF, NKL> la;
-  Bf16VecLoader<BKF, NKL> lb;
-  la.init(A, g.a_m, m0, tid);
-  lb.init(B, g.b_n, n0, tid);
-
-  f32x4 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int kq = 8 * (lane >> 4);
-  auto compute = [&](int buf) {
-    bf16x8 bh[FN], bl[FN];
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int c = (wn + j * 16 + (lane & 15)) * LDK + kq;
-      bh[j] = *reinterpret_cast<const bf16x8*>(&Bh[buf][c]);
-      bl[j] = *reinterpret_cast<const bf16x8*>(&Bl[buf][c]);
-    }
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int r = (wm + i * 16 + (lane & 15)) * LDK + kq;
-      const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&Ah[buf][r]);
-      const bf16x8 al = *reinterpret_cast<const bf16x8*>(&Al[buf][r]);
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
-      }
-    }
-  };
-
-  if (kb < ke) {
-    la.load(kb, g.K, g.kl, g.kl.sa);
-    lb.load(kb, g.K, g.kl, g.kl.sb);
-    la.store_tile(Ah[0], Al[0], kb, ke);
-    lb.store_tile(Bh[0], Bl[0], kb, ke);
-    if (kb + BK < ke) {
-      la.load(kb + BK, g.K, g.kl, g.kl.sa);
-      lb.load(kb + BK, g.K, g.kl, g.kl.sb);
-    }
-  }
-  __syncthreads();
-  int buf = 0;
-  for (int64_t kt = kb; kt < ke; kt += BK, buf ^= 1) {
-    if (kt + 2 * BK < ke) {
-      la.template store<false>(Ah[buf ^ 1], Al[buf ^ 1], kt + BK, ke);
-      lb.template store<false>(Bh[buf ^ 1], Bl[buf ^ 1], kt + BK, ke);
-      la.load(kt + 2 * BK, g.K, g.kl, g.kl.sa);
-      lb.load(kt + 2 * BK, g.K, g.kl, g.kl.sb);
-      __builtin_amdgcn_sched_barrier(0);
-    } else if (kt + BK < ke) {
-      la.store_tile(Ah[buf ^ 1], Al[buf ^ 1], kt + BK, ke);
-      lb.store_tile(Bh[buf ^ 1], Bl[buf ^ 1], kt + BK, ke);
-    }
-    compute(buf);
-    __syncthreads();
-  }
-  bf16x3_epilogue<FM, FN>(g, acc, m0, n0, wm, wn, lane, grp);
-}
-
 struct RedArgs {
   const void* P[kGettMaxGroup];
   void* C[kGettMaxGroup];
@@ -781,26 +557,10 @@ void launch_bf16x3_k(const Args& a, dim3 grid, hipStream_t s, bool akf, bool bkf
   else hipLaunchKernelGGL((gett_bf16x3_kernel<BM, BN, BK, false, false, NKL>), grid, block, 0, s, a);
 }
 
-template <int NKL>
-void launch_bf16x3_vec_k(const Args& a, dim3 grid, hipStream_t s, bool akf, bool bkf) {
-  const dim3 block(256);
-  if (akf && bkf) hipLaunchKernelGGL((gett_bf16x3_vec_kernel<true, true, NKL>), grid, block, 0, s, a);
-  else if (akf) hipLaunchKernelGGL((gett_bf16x3_vec_kernel<true, false, NKL>), grid, block, 0, s, a);
-  else if (bkf) hipLaunchKernelGGL((gett_bf16x3_vec_kernel<false, true, NKL>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gett_bf16x3_vec_kernel<false, false, NKL>), grid, block, 0, s, a);
-}
-
 template <int BM, int BN, int BK>
-void launch_bf16x3(const Args& a, int groups, int splits, hipStream_t s, bool akf, bool bkf, bool vec) {
+void launch_bf16x3(const Args& a, int groups, int splits, hipStream_t s, bool akf, bool bkf) {
   const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   const dim3 grid((unsigned)tiles, (unsigned)groups, (unsigned)splits);
-  if constexpr (BM == 128 && BN == 128 && BK == 32) {
-    if (vec) {
-      if (a.kl.n <= 2) launch_bf16x3_vec_k<2>(a, grid, s, akf, bkf);
-      else launch_bf16x3_vec_k<4>(a, grid, s, akf, bkf);
-      return;
-    }
-  }
   if (a.kl.n <= 2) launch_bf16x3_k<BM, BN, BK, 2>(a, grid, s, akf, bkf);
   else launch_bf16x3_k<BM, BN, BK, 4>(a, grid, s, akf, bkf);
 }
@@ -809,22 +569,26 @@ struct Tile {
   int bm, bn;
 };
 
+int64_t rup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
+
 // Tile shape per precision and extents. FP64: 128 x 64 (the 128 x 128 FP64 tile gives no gain at its lower
-// occupancy). FP32: among 192 x 192, 128 x 192, 192 x 128 and 128 x 128 the one with the least padding, ties to
-// the larger tile (higher arithmetic intensity; the 192 x 192 tile runs the chi = 24 steps about 5 % faster);
-// chi^2 = 576 and chi^4 extents at chi = 24 are multiples of 192 but not of 128. A 192-row (column) tile is only
-// chosen when it pads no more than a 128-row one, so the offset tables, padded to multiples of 128, cover every
-// tile. BF16X3: at most 128 x 128. 64-wide tiles for extents below 128.
-Tile choose_tile(Prec p, int64_t M, int64_t N) {
+// occupancy). FP32 matrix instructions: among 192 x 192, 128 x 192, 192 x 128 and 128 x 128 the one with the least
+// padding, ties to the larger tile; chi^2 = 576 and chi^4 extents at chi = 24 are multiples of 192 but not of 128.
+// The split kernels (`planes` > 0) the same, the FP32 form (three planes) without the 192 x 192 tile, whose second
+// sums and fragments do not fit the registers (spilling, it ran 159 TFLOP/s against 171 with 128 x 192). A 192-row (column) tile is only chosen when it pads no more than a
+// 128-row one, so the offset tables, padded to multiples of 128, cover every tile. Split-bf16 with scalar loads: at
+// most 128 x 128. 64-wide tiles for extents below 128.
+Tile choose_tile(Prec p, int64_t M, int64_t N, int planes) {
   const bool bigm = M >= 128, bign = N >= 128;
   if (p == Prec::F64) return Tile{bigm ? 128 : 64, 64};
-  if (p == Prec::BF16X3 || !bigm || !bign) return Tile{bigm ? 128 : 64, bign ? 128 : 64};
+  if ((p == Prec::BF16X3 && planes == 0) || !bigm || !bign) return Tile{bigm ? 128 : 64, bign ? 128 : 64};
   const Tile cand[4] = {{192, 192}, {128, 192}, {192, 128}, {128, 128}};
   Tile best = cand[3];
   double best_pad = 1e300;
   for (const Tile& c : cand) {
-    if (M < c.bm || N < c.bn) continue;
-    const double pad = (double)((M + c.bm - 1) / c.bm * c.bm) * (double)((N + c.bn - 1) / c.bn * c.bn);
+    if (planes == 3 && c.bm + c.bn == 384) continue;
+    if (rup(M, c.bm) > rup(M, 128) || rup(N, c.bn) > rup(N, 128)) continue;
+    const double pad = (double)rup(M, c.bm) * (double)rup(N, c.bn);
     if (pad < best_pad * (1 - 1e-12)) {
       best = c;
       best_pad = pad;
@@ -857,10 +621,27 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   a.beta = l.beta;
   a.split = 0;
 
-  const Tile tile = choose_tile(l.prec, t.M, t.N);
+  // vector tile loads when both operands' layouts allow them (planned) and every base is 16-byte aligned
+  const int vw = l.prec == Prec::F64 ? 2 : 4;
+  bool vec = t.a_vw >= vw && t.b_vw >= vw;
+  for (int g = 0; g < G; ++g)
+    vec = vec && ((uintptr_t)l.A[g] % 16 == 0) && ((uintptr_t)l.B[g] % 16 == 0);
+  // FP32 operands with vector loads and extents of 128 and more run on the bf16 matrix cores from split operands:
+  // three planes for the FP32 form (chi^9 steps at chi = 24: 172 TFLOP/s against 127 on the FP32 instructions), two
+  // for the split-bf16 form. Below 128 rows or columns a launch is bound by latency and the FP32 tiles stay. Below
+  // kSplitMinK a step is bound by writing C and both are alike (ternary maps at chi = 16 .. 32, whose composites have
+  // K = chi: 739 / 731, 3537 / 3507, 9803 / 9795, 86792 / 87555 us native / split): the FP32 instructions stay, whose
+  // 192 x 192 tile reads less. A row-walking operand's pair of k's must not straddle two values of the next
+  // contracted leg: even extent.
+  constexpr int64_t kSplitMinK = 64;
+  const bool split_ok = vec && t.M >= 128 && t.N >= 128 && t.kl.n >= 1 && t.kl.ext[0] % 2 == 0 &&
+                        (l.prec == Prec::BF16X3 || (l.prec == Prec::F32 && t.K >= kSplitMinK));
+  const int planes = split_ok ? (l.prec == Prec::F32 ? 3 : 2) : 0;
+  if (l.prec == Prec::BF16X3 && !split_ok) vec = false;
+
+  const Tile tile = choose_tile(l.prec, t.M, t.N, planes);
   const int BMsel = tile.bm, BNsel = tile.bn;
   // the m and n offset tables are padded to multiples of 128; every tile must lie within them
-  auto rup = [](int64_t x, int64_t m) { return (x + m - 1) / m * m; };
   if (rup(t.M, BMsel) > rup(t.M, 128) || rup(t.N, BNsel) > rup(t.N, 128))
     throw Error(MERA_EINVAL, "gett: tile exceeds the padded offset tables");
   const int64_t tiles = ((t.M + BMsel - 1) / BMsel) * ((t.N + BNsel - 1) / BNsel);
@@ -886,19 +667,13 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
     a.split = 1;
   }
   if (l.prepare_only) return;
-  // vector tile loads when both operands' layouts allow them (planned) and every base is 16-byte aligned
-  const int vw = l.prec == Prec::F64 ? 2 : 4;
-  bool vec = t.a_vw >= vw && t.b_vw >= vw;
-  for (int g = 0; g < G; ++g)
-    vec = vec && ((uintptr_t)l.A[g] % 16 == 0) && ((uintptr_t)l.B[g] % 16 == 0);
-  // the vector split-bf16 kernel's tile; its loads take 4 consecutive k within the fastest contracted leg
-  if (l.prec == Prec::BF16X3) vec = vec && BMsel == 128 && BNsel == 128 && t.kl.n >= 1 && t.kl.ext[0] % 4 == 0;
   hipStream_t s = ctx.stream;
   LaunchRecord rec;
   if (ctx.profiling) {
     rec.kernel = std::string("gett<") + (l.prec == Prec::F64 ? "f64" : (l.prec == Prec::F32 ? "f32" : "bf16x3")) +
                  "," + std::to_string(BMsel) + "x" + std::to_string(BNsel) + (t.a_kfast ? ",Ak" : ",Am") +
                  (t.b_kfast ? ",Bk" : ",Bn") + (vec ? ",v" : "") + (t.kl.n <= 2 ? ",k2" : ",k4") +
+                 (planes == 3 ? ",s3" : planes == 2 ? ",s2" : "") +
                  (splits > 1 ? ",splitk" : "") + (G > 1 ? ",grouped" : "") + ">";
     rec.flops = 2.0 * G * (double)t.M * (double)t.N * (double)t.K;
     rec.bytes = G * (double)eb * ((double)t.M * t.K + (double)t.K * t.N + (double)t.M * t.N * (l.beta != 0.0 ? 2 : 1));
@@ -909,7 +684,9 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   const int sel = BMsel * 1000 + BNsel;
   const bool akf = t.a_kfast, bkf = t.b_kfast;
 
-  if (l.prec == Prec::F64) {
+  if (planes > 0) {
+    launch_gett_split(a, G, splits, s, akf, bkf, BMsel, BNsel, planes);
+  } else if (l.prec == Prec::F64) {
     if (sel == 128064) launch_tile<double, 128, 64, 16>(a, G, splits, s, akf, bkf, vec);
     else launch_tile<double, 64, 64, 16>(a, G, splits, s, akf, bkf, vec);
   } else if (l.prec == Prec::F32) {
@@ -924,10 +701,10 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
     }
   } else {
     switch (sel) {
-      case 128128: launch_bf16x3<128, 128, 32>(a, G, splits, s, akf, bkf, vec); break;
-      case 128064: launch_bf16x3<128, 64, 32>(a, G, splits, s, akf, bkf, vec); break;
-      case 64128: launch_bf16x3<64, 128, 32>(a, G, splits, s, akf, bkf, vec); break;
-      default: launch_bf16x3<64, 64, 32>(a, G, splits, s, akf, bkf, vec); break;
+      case 128128: launch_bf16x3<128, 128, 32>(a, G, splits, s, akf, bkf); break;
+      case 128064: launch_bf16x3<128, 64, 32>(a, G, splits, s, akf, bkf); break;
+      case 64128: launch_bf16x3<64, 128, 32>(a, G, splits, s, akf, bkf); break;
+      default: launch_bf16x3<64, 64, 32>(a, G, splits, s, akf, bkf); break;
     }
   }
   MERA_HIP(hipGetLastError());
