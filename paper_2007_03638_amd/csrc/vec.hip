@@ -3,6 +3,7 @@
 #include "vec.h"
 
 #include <cmath>
+#include <algorithm>
 #include <unordered_map>
 
 namespace mera {
@@ -336,239 +337,300 @@ __global__ void jacobi_round_kernel(const double* __restrict__ ain, double* __re
   }
 }
 
-// Matrices up to this size are decomposed by one workgroup, with A and V in LDS and every sweep in one launch.
-constexpr int kJacobiSmall = 64;
+// ---- decompositions by one workgroup (dim <= kJacobiLds) ----------------------------------------------------
+//
+// Two launches: jacobi_rotations_kernel (one workgroup per matrix) runs the sweeps on A in LDS and records every
+// rotation; jacobi_vectors_kernel applies them to the rows of V, which are independent of each other, with one wave per
+// two rows over the whole GPU. Both are bound by latency: a round is a chain of LDS reads, one rotation's arithmetic
+// and barriers.
+//
+// A is kept in position space: position k of the tournament's ring, pairs P = (positions P and m - 1 - P), m = dim
+// rounded up to even (a dummy row and column of zeros for odd dim). The entries of the pairs P <= Q are one 2 x 2 block
+// (the other half of A is their transpose), so that the upper half of a 200 x 200 matrix fits the 160 KB of
+// LDS; a thread owns up to NBT blocks for the whole decomposition and forms J_P^T A_PQ J_Q in registers. The ring then
+// turns by one position: every entry is written to the slot of its next position, addresses that are formed once.
+// Measured: three cold 144 x 144 decompositions side by side 29.5 ms before (A and V in global memory, indices looked
+// up in every round), 2.86 ms + 0.73 ms for the vectors now; the warm-started 64 x 64 ones of an optimiser at chi = 8
+// 1.54 ms before, 0.24 ms now. A round of 144 is about 0.9 us of LDS traffic, the rest the rotations' arithmetic and the
+// barriers (512 threads with six blocks each: 3.0 ms).
+constexpr int kJacobiLds = 200;
+constexpr int kJacobiBatch = 16;
 
-// One decomposition of a batch launch (one workgroup each).
-struct JacobiSmallTask {
-  double* a;
+struct JacobiDevTask {
+  const double* a;
   double* lam;
   double* v;
-  const int* pairs;
+  double2* rot;  // (c, s) of pair P in round r: rot[r * np + P]
+  int* sweeps;   // sweeps run
   double tol;
-  int npairs, rounds, dim, max_sweeps, v_init;
+  int np, dim, max_sweeps, v_init;
 };
-constexpr int kJacobiBatch = 16;
-struct JacobiSmallBatch {
-  JacobiSmallTask t[kJacobiBatch];
+struct JacobiDevBatch {
+  JacobiDevTask t[kJacobiBatch];
 };
 
-// The same rounds and stopping rule as the multi-launch path, for dim <= kJacobiSmall, one matrix per workgroup
-// (workgroup b decomposes task b of the batch): per round the rotations of all pairs are taken from A, the 2x2
-// blocks of J^T A J are formed in registers (at most 4 blocks per thread) and written back after a barrier, and
-// V <- V J in place (each (row, pair) belongs to one thread).
-__global__ void __launch_bounds__(256) jacobi_small_kernel(JacobiSmallBatch batch) {
-  const JacobiSmallTask& task = batch.t[blockIdx.x];
-  double* const a = task.a;
-  double* const lam = task.lam;
-  double* const v = task.v;
-  const int* __restrict__ pairs = task.pairs;
-  const int npairs = task.npairs, rounds = task.rounds, dim = task.dim, max_sweeps = task.max_sweeps;
-  const int v_init = task.v_init;
-  const double tol = task.tol;
-  constexpr int LD = kJacobiSmall + 1;
-  constexpr int NB = (kJacobiSmall / 2) * (kJacobiSmall / 2) / 256;
-  __shared__ double As[kJacobiSmall * LD], Vs[kJacobiSmall * LD];
-  __shared__ double cs[kJacobiSmall / 2], sn[kJacobiSmall / 2];
-  __shared__ double part[4];
-  const int tid = threadIdx.x;
-  const int n2 = dim * dim;
-  for (int t = tid; t < n2; t += 256) {
-    const int r = t / dim, c = t - r * dim;
-    As[r * LD + c] = a[t];
-    Vs[r * LD + c] = v_init ? v[t] : (r == c ? 1.0 : 0.0);
-  }
-  __syncthreads();
-  auto block_sum = [&](double x) {
-    x = wave_sum(x);
-    if ((tid & 63) == 0) part[tid >> 6] = x;
-    __syncthreads();
-    const double tot = part[0] + part[1] + part[2] + part[3];
-    __syncthreads();
-    return tot;
-  };
-  double f2 = 0.0;
-  for (int t = tid; t < n2; t += 256) {
-    const double x = As[(t / dim) * LD + t % dim];
-    f2 += x * x;
-  }
-  const double fro = sqrt(block_sum(f2));
-  double prev_off = INFINITY;
-  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-    double o2 = 0.0;
-    for (int t = tid; t < n2; t += 256) {
-      const int r = t / dim, c = t - r * dim;
-      if (r != c) o2 += As[r * LD + c] * As[r * LD + c];
-    }
-    const double off = sqrt(block_sum(o2));
-    if (!(off > tol * fro) || dim == 1) break;
-    if (sweep >= 4 && off > 0.25 * prev_off && off < 1e-12 * fro) break;
-    prev_off = off;
-    for (int rd = 0; rd < rounds; ++rd) {
-      const int* pr = pairs + (size_t)rd * npairs * 2;
-      if (tid < npairs) {
-        double c, s;
-        rot_of(As, LD, pr[2 * tid], pr[2 * tid + 1], c, s);
-        cs[tid] = c;
-        sn[tid] = s;
-      }
-      __syncthreads();
-      double nv[NB][4];
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        const int id = tid + q * 256;
-        if (id < npairs * npairs) {
-          const int P = id / npairs, Q = id - P * npairs;
-          const int i = pr[2 * P], j = pr[2 * P + 1], k = pr[2 * Q], l = pr[2 * Q + 1];
-          const double cp = cs[P], sp = sn[P], cq = cs[Q], sq = sn[Q];
-          const double aik = (i >= 0 && k >= 0) ? As[i * LD + k] : 0.0;
-          const double ail = (i >= 0 && l >= 0) ? As[i * LD + l] : 0.0;
-          const double ajk = (j >= 0 && k >= 0) ? As[j * LD + k] : 0.0;
-          const double ajl = (j >= 0 && l >= 0) ? As[j * LD + l] : 0.0;
-          const double t0k = cp * aik - sp * ajk, t0l = cp * ail - sp * ajl;
-          const double t1k = sp * aik + cp * ajk, t1l = sp * ail + cp * ajl;
-          nv[q][0] = cq * t0k - sq * t0l;
-          nv[q][1] = (P == Q) ? 0.0 : sq * t0k + cq * t0l;
-          nv[q][2] = (P == Q) ? 0.0 : cq * t1k - sq * t1l;
-          nv[q][3] = sq * t1k + cq * t1l;
-        }
-      }
-      for (int id = tid; id < dim * npairs; id += 256) {
-        const int r = id / npairs, P = id - r * npairs;
-        const int i = pr[2 * P], j = pr[2 * P + 1];
-        if (i >= 0 && j >= 0) {
-          const double vi = Vs[r * LD + i], vj = Vs[r * LD + j];
-          Vs[r * LD + i] = cs[P] * vi - sn[P] * vj;
-          Vs[r * LD + j] = sn[P] * vi + cs[P] * vj;
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        const int id = tid + q * 256;
-        if (id < npairs * npairs) {
-          const int P = id / npairs, Q = id - P * npairs;
-          const int i = pr[2 * P], j = pr[2 * P + 1], k = pr[2 * Q], l = pr[2 * Q + 1];
-          if (i >= 0 && k >= 0) As[i * LD + k] = nv[q][0];
-          if (i >= 0 && l >= 0) As[i * LD + l] = nv[q][1];
-          if (j >= 0 && k >= 0) As[j * LD + k] = nv[q][2];
-          if (j >= 0 && l >= 0) As[j * LD + l] = nv[q][3];
-        }
-      }
-      __syncthreads();
-    }
-  }
-  for (int t = tid; t < dim; t += 256) lam[t] = As[t * LD + t];
-  for (int t = tid; t < n2; t += 256) {
-    const int r = t / dim, c = t - r * dim;
-    a[t] = As[r * LD + c];
-    v[t] = Vs[r * LD + c];
+// Rotation that zeroes the off-diagonal entry of a pair (Golub & Van Loan's symmetric Schur step). The angle comes from
+// the hardware's reciprocal and square-root estimates (about 1e-7: the rotated entry is computed, not set to zero,
+// and shrinks by that factor), c = (1 + t^2)^{-1/2} is refined by two Newton steps, so that c^2 + s^2 = 1 to rounding.
+__device__ inline double2 jacobi_rotation(double aii, double aij, double ajj) {
+  if (!(fabs(aij) > 0x1p-1000) && aij == aij) return double2{1.0, 0.0};
+  const double tau = (ajj - aii) * __builtin_amdgcn_rcp(2.0 * aij);
+  const double r = __builtin_amdgcn_rcp(fabs(tau) + __builtin_amdgcn_sqrt(1.0 + tau * tau));
+  const double t = tau >= 0.0 ? r : (tau < 0.0 ? -r : tau);  // NaN stays NaN
+  const double x = 1.0 + t * t;
+  double c = __builtin_amdgcn_rsq(x);
+  c = c * (1.5 - 0.5 * x * c * c);
+  c = c * (1.5 - 0.5 * x * c * c);
+  return double2{c, t * c};
+}
+
+// next slot of (pair P, top or bottom): the ring turns positions 1 .. m - 1 by one, position 0 stays
+__device__ inline void jacobi_next_slot(int np, int P, int bottom, int& P2, int& bottom2) {
+  if (!bottom) {
+    P2 = P == 0 ? 0 : (P == np - 1 ? np - 1 : P + 1);
+    bottom2 = (P > 0 && P == np - 1) ? 1 : 0;
+  } else if (P == 0) {
+    P2 = np > 1 ? 1 : 0;
+    bottom2 = np > 1 ? 0 : 1;
+  } else {
+    P2 = P - 1;
+    bottom2 = 1;
   }
 }
 
-// Matrices above kJacobiSmall and up to this size are decomposed by one workgroup of kMidThreads threads each, A
-// (ping-pong) and V in global memory (L2-resident at these sizes), every sweep in one launch: no launch per round
-// and no host synchronisation per sweep, and the matrices of one batch run side by side. A round's work grows
-// as dim^2 on one workgroup, so above this size the per-round launches over the whole GPU are faster.
-constexpr int kJacobiMid = 160;
-constexpr int kMidThreads = 1024;
+__device__ inline int jacobi_block(int np, int P, int Q) { return P * np - P * (P - 1) / 2 + (Q - P); }  // P <= Q
 
-struct JacobiMidTask {
-  double* a;  // in: the matrix; out: the rotated matrix (diagonal = eigenvalues)
-  double* b;  // ping-pong buffer, dim x dim
-  double* lam;
-  double* v;
-  const int* pairs;
-  double tol;
-  int npairs, rounds, dim, max_sweeps, v_init;
-};
-struct JacobiMidBatch {
-  JacobiMidTask t[kJacobiBatch];
-};
+// place of entry (row slot (P, x), column slot (Q, y)): entry 2 x + y of the block, each of the four entries an array
+// over the blocks (`stride` apart), so that neighbouring threads read and write neighbouring words; the diagonal
+// blocks use entries 0, 1 and 3
+__device__ inline int jacobi_place(int np, int stride, int P, int x, int Q, int y) {
+  if (P > Q || (P == Q && x > y)) {
+    const int p = P, q = x;
+    P = Q;
+    x = y;
+    Q = p;
+    y = q;
+  }
+  return (2 * x + y) * stride + jacobi_block(np, P, Q);
+}
 
-// The rounds, rotations and block updates of jacobi_round_kernel, and the stopping rule of the multi-launch path
-// (off-diagonal and Frobenius norms summed in the workgroup), with a barrier between rounds.
-__global__ void __launch_bounds__(kMidThreads) jacobi_mid_kernel(JacobiMidBatch batch) {
-  const JacobiMidTask& task = batch.t[blockIdx.x];
-  const int dim = task.dim, npairs = task.npairs, rounds = task.rounds;
-  const int* __restrict__ pairs = task.pairs;
-  double* const v = task.v;
-  __shared__ double cs[kJacobiMid / 2], sn[kJacobiMid / 2];
-  __shared__ double part[kMidThreads / 64];
+template <int NPMAX, int THREADS, int NBT>
+__global__ void __launch_bounds__(THREADS) jacobi_rotations_kernel(JacobiDevBatch batch) {
+  static_assert(NPMAX * (NPMAX + 1) / 2 <= THREADS * NBT, "blocks per thread");
+  const JacobiDevTask& task = batch.t[blockIdx.x];
+  const int np = task.np, dim = task.dim, m = 2 * np;
+  const int nblk = np * (np + 1) / 2;
+  constexpr int NB = NPMAX * (NPMAX + 1) / 2;
+  __shared__ double blk[4 * NB];
+  __shared__ __attribute__((aligned(16))) double2 cs[NPMAX];
+  __shared__ double red[THREADS / 64];
   const int tid = threadIdx.x;
-  const int64_t n2 = (int64_t)dim * dim;
-  auto block_sum = [&](double x) {
+
+  int bp[NBT], bq[NBT], dst[NBT][4];  // the thread's blocks and the places their entries move to
+#pragma unroll
+  for (int q = 0; q < NBT; ++q) {
+    const int id = tid + q * THREADS;
+    int P = 0, first = 0;
+    while (P + 1 < np && first + (np - P) <= id) {
+      first += np - P;
+      ++P;
+    }
+    const int Q = P + (id - first);
+    bp[q] = P;
+    bq[q] = Q;
+    if (id < nblk) {
+      int P2[2], x2[2], Q2[2], y2[2];
+      for (int x = 0; x < 2; ++x) {
+        jacobi_next_slot(np, P, x, P2[x], x2[x]);
+        jacobi_next_slot(np, Q, x, Q2[x], y2[x]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dst[q][e] = jacobi_place(np, NB, P2[e >> 1], x2[e >> 1], Q2[e & 1], y2[e & 1]);
+      // position = index before the first round
+      const int r[2] = {P, m - 1 - P}, c[2] = {Q, m - 1 - Q};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = r[e >> 1], j = c[e & 1];
+        blk[e * NB + id] = (i < dim && j < dim) ? task.a[(int64_t)i * dim + j] : 0.0;
+      }
+    }
+  }
+  __syncthreads();
+
+  auto total = [&](double x) {
     x = wave_sum(x);
-    if ((tid & 63) == 0) part[tid >> 6] = x;
+    if ((tid & 63) == 0) red[tid >> 6] = x;
     __syncthreads();
-    double tot = 0.0;
-    for (int w = 0; w < kMidThreads / 64; ++w) tot += part[w];
+    double t = 0.0;
+    for (int w = 0; w < THREADS / 64; ++w) t += red[w];
     __syncthreads();
-    return tot;
+    return t;
   };
-  if (!task.v_init)
-    for (int64_t t = tid; t < n2; t += kMidThreads) v[t] = (t / dim == t % dim) ? 1.0 : 0.0;
-  double* cur = task.a;
-  double* nxt = task.b;
-  double f2 = 0.0;
-  for (int64_t t = tid; t < n2; t += kMidThreads) f2 += cur[t] * cur[t];
-  const double fro = sqrt(block_sum(f2));
+  // squares of the diagonal and (twice) of the entries above it
+  double d2 = 0.0;
+  auto squares = [&](bool diagonal) {
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < NBT; ++q) {
+      const int id = tid + q * THREADS;
+      if (id < nblk) {
+        const double b0 = blk[id], b1 = blk[NB + id], b2 = blk[2 * NB + id], b3 = blk[3 * NB + id];
+        if (bp[q] == bq[q]) {
+          s += 2.0 * b1 * b1;
+          if (diagonal) s += b0 * b0 + b3 * b3;
+        } else {
+          s += 2.0 * (b0 * b0 + b1 * b1 + b2 * b2 + b3 * b3);
+        }
+      }
+    }
+    return s;
+  };
+  d2 = total(squares(true));
+  const double fro = sqrt(d2);
   double prev_off = INFINITY;
-  for (int sweep = 0; sweep < task.max_sweeps; ++sweep) {
-    double o2 = 0.0;
-    for (int64_t t = tid; t < n2; t += kMidThreads)
-      if (t / dim != t % dim) o2 += cur[t] * cur[t];
-    const double off = sqrt(block_sum(o2));
+  double2* rot = task.rot;
+  int sweep = 0;
+  for (; sweep < task.max_sweeps; ++sweep) {
+    const double off = sqrt(total(squares(false)));
     if (!(off > task.tol * fro) || dim == 1) break;
     // rounding floor: off-diagonal mass no longer shrinks quadratically
     if (sweep >= 4 && off > 0.25 * prev_off && off < 1e-12 * fro) break;
     prev_off = off;
-    for (int rd = 0; rd < rounds; ++rd) {
-      const int* pr = pairs + (size_t)rd * npairs * 2;
-      if (tid < npairs) {
-        double c, s;
-        rot_of(cur, dim, pr[2 * tid], pr[2 * tid + 1], c, s);
-        cs[tid] = c;
-        sn[tid] = s;
+    for (int rd = 0; rd < m - 1; ++rd) {
+      for (int P = tid; P < np; P += THREADS) {
+        const double* b = blk + jacobi_block(np, P, P);
+        const double2 x = jacobi_rotation(b[0], b[NB], b[3 * NB]);
+        cs[P] = x;
+        rot[P] = x;
       }
+      rot += np;
       __syncthreads();
-      for (int id = tid; id < npairs * npairs; id += kMidThreads) {
-        const int P = id / npairs, Q = id - P * npairs;
-        const int i = pr[2 * P], j = pr[2 * P + 1], k = pr[2 * Q], l = pr[2 * Q + 1];
-        const double cp = cs[P], sp = sn[P], cq = cs[Q], sq = sn[Q];
-        double aik = (i >= 0 && k >= 0) ? cur[(int64_t)i * dim + k] : 0.0;
-        double ail = (i >= 0 && l >= 0) ? cur[(int64_t)i * dim + l] : 0.0;
-        double ajk = (j >= 0 && k >= 0) ? cur[(int64_t)j * dim + k] : 0.0;
-        double ajl = (j >= 0 && l >= 0) ? cur[(int64_t)j * dim + l] : 0.0;
-        double t0k = cp * aik - sp * ajk, t0l = cp * ail - sp * ajl;
-        double t1k = sp * aik + cp * ajk, t1l = sp * ail + cp * ajl;
-        double n_ik = cq * t0k - sq * t0l, n_il = sq * t0k + cq * t0l;
-        double n_jk = cq * t1k - sq * t1l, n_jl = sq * t1k + cq * t1l;
-        if (P == Q) { n_il = 0.0; n_jk = 0.0; }
-        if (i >= 0 && k >= 0) nxt[(int64_t)i * dim + k] = n_ik;
-        if (i >= 0 && l >= 0) nxt[(int64_t)i * dim + l] = n_il;
-        if (j >= 0 && k >= 0) nxt[(int64_t)j * dim + k] = n_jk;
-        if (j >= 0 && l >= 0) nxt[(int64_t)j * dim + l] = n_jl;
-      }
-      for (int id = tid; id < dim * npairs; id += kMidThreads) {
-        const int r = id / npairs, P = id - r * npairs;
-        const int i = pr[2 * P], j = pr[2 * P + 1];
-        if (i >= 0 && j >= 0) {
-          const double cp = cs[P], sp = sn[P];
-          const double vi = v[(int64_t)r * dim + i], vj = v[(int64_t)r * dim + j];
-          v[(int64_t)r * dim + i] = cp * vi - sp * vj;
-          v[(int64_t)r * dim + j] = sp * vi + cp * vj;
+      double n[NBT][4];
+#pragma unroll
+      for (int q = 0; q < NBT; ++q) {
+        const int id = tid + q * THREADS;
+        if (id < nblk) {
+          const double2 p = cs[bp[q]], r = cs[bq[q]];
+          const bool diag = bp[q] == bq[q];
+          const double aik = blk[id], ail = blk[NB + id], ajk = blk[(diag ? NB : 2 * NB) + id], ajl = blk[3 * NB + id];
+          const double t0k = p.x * aik - p.y * ajk, t0l = p.x * ail - p.y * ajl;
+          const double t1k = p.y * aik + p.x * ajk, t1l = p.y * ail + p.x * ajl;
+          n[q][0] = r.x * t0k - r.y * t0l;
+          n[q][1] = r.y * t0k + r.x * t0l;
+          n[q][2] = diag ? n[q][1] : r.x * t1k - r.y * t1l;
+          n[q][3] = r.y * t1k + r.x * t1l;
         }
       }
       __syncthreads();
-      double* t = cur;
-      cur = nxt;
-      nxt = t;
+#pragma unroll
+      for (int q = 0; q < NBT; ++q)
+        if (tid + q * THREADS < nblk) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) blk[dst[q][e]] = n[q][e];
+        }
+      __syncthreads();
     }
   }
-  for (int t = tid; t < dim; t += kMidThreads) task.lam[t] = cur[(int64_t)t * dim + t];
-  if (cur != task.a)
-    for (int64_t t = tid; t < n2; t += kMidThreads) task.a[t] = cur[t];
+  if (tid == 0) *task.sweeps = sweep;
+  // a sweep of m - 1 rounds brings every index back to its own position
+  for (int P = tid; P < np; P += THREADS) {
+    const double* b = blk + jacobi_block(np, P, P);
+    task.lam[P] = b[0];
+    if (m - 1 - P < dim) task.lam[m - 1 - P] = b[3 * NB];
+  }
+}
+
+// V <- V J for all recorded rotations: a wave owns kVecRows rows, in LDS; lane l rotates pairs l and l + 64. The LDS
+// operations of one wave complete in order, so the rounds need no barrier. The rotations come from beyond L2 (another
+// XCD wrote them), 2 us away: the workgroup loads kVecChunk rounds at a time, a chunk ahead of its use.
+constexpr int kVecRows = 2, kVecChunk = 16, kVecWaves = 4;
+constexpr int kVecLoads = (kVecChunk * (kJacobiLds / 2) + 64 * kVecWaves - 1) / (64 * kVecWaves);
+
+__global__ void __launch_bounds__(64 * kVecWaves) jacobi_vectors_kernel(JacobiDevBatch batch) {
+  const JacobiDevTask& task = batch.t[blockIdx.y];
+  const int np = task.np, dim = task.dim, m = 2 * np;
+  if ((int)blockIdx.x * kVecWaves * kVecRows >= dim) return;  // (whole workgroups)
+  constexpr int LD = kJacobiLds + 2;  // two entries for the lanes without a pair
+  __shared__ double rows[kVecWaves][kVecRows][LD];
+  __shared__ __attribute__((aligned(16))) double2 rots[2][kVecChunk * (kJacobiLds / 2)];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r0 = (blockIdx.x * kVecWaves + wave) * kVecRows;
+  double (&x)[kVecRows][LD] = rows[wave];
+#pragma unroll
+  for (int r = 0; r < kVecRows; ++r)
+    for (int k = lane; k < LD; k += 64)
+      x[r][k] = (r0 + r < dim && k < dim)
+                    ? (task.v_init ? task.v[(int64_t)(r0 + r) * dim + k] : (r0 + r == k ? 1.0 : 0.0)) : 0.0;
+  const int rounds = *task.sweeps * (m - 1);
+  const int count = rounds * np, per = kVecChunk * np;  // rotations in all and in a chunk
+  double2 st[kVecLoads];
+  auto fetch = [&](int first) {
+#pragma unroll
+    for (int q = 0; q < kVecLoads; ++q) {
+      const int e = tid + q * 64 * kVecWaves;
+      if (e < per && first + e < count) st[q] = task.rot[first + e];
+    }
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < kVecLoads; ++q) {
+      const int e = tid + q * 64 * kVecWaves;
+      if (e < per) rots[buf][e] = st[q];
+    }
+  };
+  // indices at the pair's two positions; after every round they fall by one, 1 being followed by m - 1 (0 stays). No
+  // branches: lanes without a pair rotate two entries of their own that nothing reads.
+  int i[2], j[2], di[2], dj[2], at[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int P = lane + 64 * h;
+    const bool on = P < np;
+    i[h] = on ? P : kJacobiLds;
+    j[h] = on ? m - 1 - P : kJacobiLds + 1;
+    di[h] = on && P > 0 ? 1 : 0;
+    dj[h] = on ? 1 : 0;
+    at[h] = on ? P : 0;
+  }
+  fetch(0);
+  put(0);
+  __syncthreads();
+  int buf = 0;
+  for (int rd = 0; rd < rounds; rd += kVecChunk, buf ^= 1) {
+    fetch((rd + kVecChunk) * np);
+    const int n = rounds - rd < kVecChunk ? rounds - rd : kVecChunk;
+    for (int a = 0; a < n; ++a) {
+      // all reads of a round before its writes (no two lanes or halves share an entry): one LDS latency per round
+      double2 c[2];
+      double vi[2][kVecRows], vj[2][kVecRows];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        c[h] = rots[buf][a * np + at[h]];
+#pragma unroll
+        for (int r = 0; r < kVecRows; ++r) {
+          vi[h][r] = x[r][i[h]];
+          vj[h][r] = x[r][j[h]];
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int r = 0; r < kVecRows; ++r) {
+          x[r][i[h]] = c[h].x * vi[h][r] - c[h].y * vj[h][r];
+          x[r][j[h]] = c[h].y * vi[h][r] + c[h].x * vj[h][r];
+        }
+        i[h] = i[h] == 1 ? m - 1 : i[h] - di[h];
+        j[h] = j[h] == 1 ? m - 1 : j[h] - dj[h];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    put(buf ^ 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < kVecRows; ++r)
+    if (r0 + r < dim)
+      for (int k = lane; k < dim; k += 64) task.v[(int64_t)(r0 + r) * dim + k] = x[r][k];
 }
 
 __global__ void offdiag_kernel(const double* a, int dim, double* out) {
@@ -1036,56 +1098,57 @@ JacobiSchedule& jacobi_schedule(Ctx& ctx, int dim) {
 
 }  // namespace
 
-// The multi-launch path (one kernel per round) for matrices above kJacobiMid.
+// The multi-launch path (one kernel per round) for matrices above kJacobiLds.
 void jacobi_eigh_rounds(Ctx& ctx, double* a, double* lam, double* v, int dim, double tol, int max_sweeps,
                         bool v_init);
 
 void jacobi_eigh_batch(Ctx& ctx, const std::vector<JacobiTask>& tasks) {
-  JacobiSmallBatch batch{};
-  JacobiMidBatch mid{};
-  int nb = 0, nm = 0;
-  auto flush = [&]() {
-    if (nb == 0) return;
-    hipLaunchKernelGGL(jacobi_small_kernel, dim3(nb), dim3(256), 0, ctx.stream, batch);
-    MERA_HIP(hipGetLastError());
-    nb = 0;
-  };
-  auto flush_mid = [&]() {
-    if (nm == 0) return;
-    hipLaunchKernelGGL(jacobi_mid_kernel, dim3(nm), dim3(kMidThreads), 0, ctx.stream, mid);
-    MERA_HIP(hipGetLastError());
-    nm = 0;
-  };
-  for (const JacobiTask& t : tasks) {
-    if (t.dim <= 0) continue;
-    if (t.dim > kJacobiMid) {
-      jacobi_eigh_rounds(ctx, t.a, t.lam, t.v, t.dim, t.tol, t.max_sweeps, t.v_init);
-      continue;
-    }
-    JacobiSchedule& s = jacobi_schedule(ctx, t.dim);
-    if (t.dim <= kJacobiSmall) {
-      batch.t[nb++] = JacobiSmallTask{t.a, t.lam, t.v, s.pairs.as<int>(), t.tol, s.npairs, s.rounds, t.dim,
-                                      t.max_sweeps, t.v_init ? 1 : 0};
+  // size classes of the one-workgroup kernel: largest pair count, and how its blocks are spread over threads. A smaller
+  // workgroup passes a barrier sooner; above 154 rows the blocks no longer fit three to a thread.
+  constexpr int kClasses = 5;
+  const int np_max[kClasses] = {10, 22, 32, 77, 100};
+  for (int cl = 0; cl < kClasses; ++cl) {
+    JacobiDevBatch batch{};
+    int nb = 0, dmax = 0;
+    auto flush = [&]() {
+      if (nb == 0) return;
+      const dim3 g(nb);
+      switch (cl) {
+        case 0: hipLaunchKernelGGL((jacobi_rotations_kernel<10, 64, 1>), g, dim3(64), 0, ctx.stream, batch); break;
+        case 1: hipLaunchKernelGGL((jacobi_rotations_kernel<22, 256, 1>), g, dim3(256), 0, ctx.stream, batch); break;
+        case 2: hipLaunchKernelGGL((jacobi_rotations_kernel<32, 576, 1>), g, dim3(576), 0, ctx.stream, batch); break;
+        case 3: hipLaunchKernelGGL((jacobi_rotations_kernel<77, 1024, 3>), g, dim3(1024), 0, ctx.stream, batch); break;
+        default: hipLaunchKernelGGL((jacobi_rotations_kernel<100, 1024, 5>), g, dim3(1024), 0, ctx.stream, batch);
+      }
+      MERA_HIP(hipGetLastError());
+      const int rows = kVecWaves * kVecRows;
+      hipLaunchKernelGGL(jacobi_vectors_kernel, dim3((dmax + rows - 1) / rows, nb), dim3(64 * kVecWaves), 0, ctx.stream,
+                         batch);
+      MERA_HIP(hipGetLastError());
+      nb = dmax = 0;
+    };
+    for (const JacobiTask& t : tasks) {
+      if (t.dim <= 0 || t.dim > kJacobiLds) continue;
+      const int np = (t.dim + 1) / 2;
+      if (np > np_max[cl] || (cl > 0 && np <= np_max[cl - 1])) continue;
+      // per-slot scratch, shared by all launches on the context's stream
+      const size_t rounds = (size_t)std::max(t.max_sweeps, 1) * (size_t)(2 * np - 1);
+      char* scratch = static_cast<char*>(ctx.buf("jacobi.rot" + std::to_string(nb),
+                                                 16 + rounds * (size_t)np * sizeof(double2)));
+      batch.t[nb++] = JacobiDevTask{t.a, t.lam, t.v, reinterpret_cast<double2*>(scratch + 16),
+                                    reinterpret_cast<int*>(scratch), t.tol, np, t.dim, t.max_sweeps, t.v_init ? 1 : 0};
+      dmax = std::max(dmax, t.dim);
       if (nb == kJacobiBatch) flush();
-    } else {
-      double* b = static_cast<double*>(ctx.buf("jacobi.mid" + std::to_string(nm),
-                                               (size_t)t.dim * t.dim * sizeof(double)));
-      mid.t[nm++] = JacobiMidTask{t.a, b, t.lam, t.v, s.pairs.as<int>(), t.tol, s.npairs, s.rounds, t.dim,
-                                  t.max_sweeps, t.v_init ? 1 : 0};
-      if (nm == kJacobiBatch) flush_mid();
     }
+    flush();
   }
-  flush();
-  flush_mid();
+  for (const JacobiTask& t : tasks)
+    if (t.dim > kJacobiLds) jacobi_eigh_rounds(ctx, t.a, t.lam, t.v, t.dim, t.tol, t.max_sweeps, t.v_init);
 }
 
 void jacobi_eigh(Ctx& ctx, double* a, double* lam, double* v, int dim, double tol, int max_sweeps, bool v_init) {
   if (dim <= 0) return;
-  if (dim <= kJacobiMid) {
-    jacobi_eigh_batch(ctx, {JacobiTask{a, lam, v, dim, tol, max_sweeps, v_init}});
-    return;
-  }
-  jacobi_eigh_rounds(ctx, a, lam, v, dim, tol, max_sweeps, v_init);
+  jacobi_eigh_batch(ctx, {JacobiTask{a, lam, v, dim, tol, max_sweeps, v_init}});
 }
 
 void jacobi_eigh_rounds(Ctx& ctx, double* a, double* lam, double* v, int dim, double tol, int max_sweeps,
