@@ -16,7 +16,7 @@ namespace mera {
 // K index as a mixed-radix number over the contracted legs, fastest leg first: k = d_0 + ext_0 (d_1 + ext_1 (...)),
 // so &A[., k] adds sum_l d_l sa[l] and &B[k, .] adds sum_l d_l sb[l]. The kernels form these offsets
 // arithmetically (no table, no memory load): q / ext_l = mulhi(q, mag_l) with mag_l = ceil(2^32 / ext_l), exact
-// because every quotient q met satisfies q * ext_l <= 2^32 (checked when the legs are built); the slowest leg has
+// because every quotient q met satisfies q * (mag_l ext_l - 2^32) < 2^32 (checked when the legs are built); the slowest leg has
 // mag 0 (its digit is the whole remaining quotient). Legs of extent 1 are dropped and legs contiguous in both
 // operands merged; unused entries are zero. Strides are 32-bit (in elements, checked when the legs are built); the
 // digits are formed in 32-bit arithmetic and each digit-stride product is accumulated into a 64-bit offset.

@@ -10,8 +10,8 @@
 // to its accumulator at a time, cut (towards minus infinity) at 2^-26 of the largest of them, so that products added
 // straight to a long sum lose their low bits and leave a bias; measured over K = 13824, error against 64 bits 1.9e-6
 // that way, 5.8e-7 with fresh sums and 2.2e-6 on the FP32 matrix instructions (K = 576: 3.8e-7, 1.3e-7, 4.5e-7). What
-// bias the cut leaves within 16 k's is turned round in every other tile, whose A is staged negated and whose sums
-// are subtracted (over K = 331776 of random signs it had been a third of the error).
+// bias the cut leaves within 16 k's is turned round in every other tile, of which one operand is staged negated and the
+// sums subtracted (over K = 331776 of random signs it had been a third of the error).
 // planes = 2 (the split-bf16 form): x ~ hi + lo, products lo hi, hi lo, hi hi.
 //
 // What bounds it: the bf16 matrix cores and the power they draw. 2.5 PFLOP/s / 6 = 417 TFLOP/s of contraction arithmetic in the FP32 form
@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(256, 2) gett_split_kernel(GettArgs g) {
     if (NP == 3) part[s & 1] = t;
     else c = t;
   };
-  // adds the sums of block s of a tile whose A is staged with this sign
+  // adds the sums of block s of a tile staged with this sign
   auto flush = [&](int s, float sign) {
     if (NP == 3) {
       const int o = s / NI, i = s % NI;
@@ -252,7 +252,8 @@ __global__ void __launch_bounds__(256, 2) gett_split_kernel(GettArgs g) {
   // tile t + 1, in registers since tile t - 1, is split and staged into the other buffer piece by piece over the
   // slots before the barrier (TAIL: with zeros past the end), each unit of registers being reloaded from tile t + 2
   // as soon as it is staged, so that a load has about a tile's time. Every wave runs the same number of barriers.
-  // In the FP32 form the odd tiles hold -A (FLIP: this wave stages A).
+  // In the FP32 form one operand's odd tiles are staged negated (FLIP: by this wave): the one with fewer rows, so that
+  // neither team has much more to do than the other (with 192 x 128 tiles: chi^9 step 29.6 ms against 33.2).
   auto tile = [&](auto tail_tag, auto flip_tag, auto& ld, int64_t kt, int buf, __bf16* lds, const uint32_t* stride) {
     constexpr bool TAIL = decltype(tail_tag)::value;
     constexpr bool FLIP = NP == 3 && decltype(flip_tag)::value;
@@ -308,11 +309,11 @@ __global__ void __launch_bounds__(256, 2) gett_split_kernel(GettArgs g) {
   if (wave < 2) {
     SplitLoader<AKF, BM, NKL, NP> ld;
     ld.init(A, g.a_m, m0, tid & 127);
-    loop(std::true_type{}, ld, As[0], g.kl.sa);
+    loop(std::integral_constant<bool, (BM <= BN)>{}, ld, As[0], g.kl.sa);
   } else {
     SplitLoader<BKF, BN, NKL, NP> ld;
     ld.init(B, g.b_n, n0, tid & 127);
-    loop(std::false_type{}, ld, Bs[0], g.kl.sb);
+    loop(std::integral_constant<bool, (BM > BN)>{}, ld, Bs[0], g.kl.sb);
   }
 
   // epilogue (acc[i] -> row 8 (i / 4) + 4 (lane / 32) + i % 4, column lane % 32)

@@ -157,6 +157,13 @@ void fill_table(std::vector<int64_t>& out, const std::string& legs, const LegDim
   }
 }
 
+// Whether q / e = mulhi(q, ceil(2^32 / e)) for every q <= qmax: the multiplier exceeds 2^32 / e by excess / (2^32 e) per
+// unit, which must not carry a quotient over the next integer.
+bool reciprocal_exact(uint64_t qmax, uint64_t e) {
+  const uint64_t mag = ((uint64_t(1) << 32) + e - 1) / e, excess = mag * e - (uint64_t(1) << 32);
+  return mag < (uint64_t(1) << 32) && (excess == 0 || qmax < (uint64_t(1) << 32) / excess);
+}
+
 // Contracted legs as a mixed-radix k index for the kernels, fastest first (the last leg of `Kl` is the fastest):
 // legs of extent 1 are dropped, and a leg that continues the previous one contiguously in both operands is merged
 // into it. Each leg's reciprocal multiplier is checked exact for every quotient the kernels will form; the slowest
@@ -167,15 +174,21 @@ GettKLegs k_legs(const std::string& prog, const std::string& Kl, const LegDims& 
     int64_t ext, xa, xb;
   };
   std::vector<Leg> legs;
+  int64_t faster = 1;  // product of the extents of the legs before legs.back()
   for (int i = (int)Kl.size() - 1; i >= 0; --i) {
     const char c = Kl[i];
     const int64_t e = dims[(unsigned char)c];
     if (e == 1) continue;
     const int64_t xa = stride_of(LA, sa, c), xb = stride_of(LB, sb, c);
-    if (!legs.empty() && legs.back().xa * legs.back().ext == xa && legs.back().xb * legs.back().ext == xb)
-      legs.back().ext *= e;
-    else
+    // a merged leg must still be divided by exactly (checked below), unless it is the slowest
+    const int64_t merged = legs.empty() ? 0 : legs.back().ext * e;
+    if (!legs.empty() && legs.back().xa * legs.back().ext == xa && legs.back().xb * legs.back().ext == xb &&
+        (faster * merged == K || reciprocal_exact((uint64_t)((K - 1) / faster), (uint64_t)merged))) {
+      legs.back().ext = merged;
+    } else {
+      if (!legs.empty()) faster *= legs.back().ext;
       legs.push_back(Leg{e, xa, xb});
+    }
   }
   if ((int)legs.size() > kGettMaxKLegs)
     throw Error(MERA_EINVAL, prog + ": more than " + std::to_string(kGettMaxKLegs) + " contracted legs");
@@ -191,7 +204,7 @@ GettKLegs k_legs(const std::string& prog, const std::string& Kl, const LegDims& 
     kl.ext[l] = (uint32_t)e;
     if (l + 1 < kl.n) {
       const uint64_t qmax = (uint64_t)(K - 1) / (uint64_t)below;  // largest quotient entering leg l
-      if (qmax * e > (uint64_t(1) << 32)) throw Error(MERA_EINVAL, prog + ": contracted leg too large");
+      if (!reciprocal_exact(qmax, e)) throw Error(MERA_EINVAL, prog + ": contracted leg too large");
       kl.mag[l] = (uint32_t)(((uint64_t(1) << 32) + e - 1) / e);
     }  // the slowest leg takes the whole remaining quotient: mag 0 (no division)
     kl.sa[l] = (uint32_t)legs[l].xa;
@@ -279,6 +292,12 @@ PlanCache::Entry& plan_step(Ctx& ctx, const Program& prog, size_t si, const LegD
     for (char c : LB)
       if (has(Kl, c)) k2 += c;
     Kl = k2;
+  }
+  // An operand read along K may take its free legs in any order: the one that is C's unit-stride leg becomes the
+  // fastest, so that the lanes, which run along N, store C coalesced.
+  if (b_kfast && Nl.size() > 1 && has(Nl, s.lc.back()) && Nl.back() != s.lc.back()) {
+    Nl.erase(Nl.find(s.lc.back()), 1);
+    Nl += s.lc.back();
   }
   auto ext = [&](const std::string& legs) {
     int64_t t = 1;
