@@ -597,6 +597,19 @@ Tile choose_tile(Prec p, int64_t M, int64_t N, int planes) {
   return best;
 }
 
+// Estimated microseconds of `tiles` output tiles in `splits` k ranges: rounds of 512 workgroups (two per CU; up to 256
+// more, alone on their CUs, take three quarters of a round) at `rate` flop/us over the chip, and, if split, writing and
+// adding the partial sums (0.4 us per MB) in a second launch. Fitted to 2000 timings of the programs' contractions at
+// chi = 4 .. 20, within 15 % at the median. Filling whole rounds is what it is for: FP32 20736 x 144 x 1728 (162 tiles)
+// 128 us in two ranges, 105 in three; the 324 tiles of the isometry derivative at chi = 24 in 4 ranges fill 2.5 rounds.
+double split_cost(int64_t tiles, int splits, const GettTables& t, const Tile& tile, double rate, size_t eb) {
+  const int64_t blocks = tiles * splits, rem = blocks % 512;
+  const double rounds = (double)(blocks / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 0.75 : 1.0);
+  const double kc = (double)rup((t.K + splits - 1) / splits, 32);
+  const double red = splits > 1 ? 9.5 + 0.4e-6 * splits * (double)t.M * (double)t.N * (double)eb : 0.0;
+  return rounds * kc * 2.0 * tile.bm * tile.bn * 512 / rate + red;
+}
+
 }  // namespace
 
 void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
@@ -623,9 +636,12 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
 
   // vector tile loads when both operands' layouts allow them (planned) and every base is 16-byte aligned
   const int vw = l.prec == Prec::F64 ? 2 : 4;
-  bool vec = t.a_vw >= vw && t.b_vw >= vw;
-  for (int g = 0; g < G; ++g)
-    vec = vec && ((uintptr_t)l.A[g] % 16 == 0) && ((uintptr_t)l.B[g] % 16 == 0);
+  bool a16 = t.a_vw >= vw, b16 = t.b_vw >= vw;
+  for (int g = 0; g < G; ++g) {
+    a16 = a16 && (uintptr_t)l.A[g] % 16 == 0;
+    b16 = b16 && (uintptr_t)l.B[g] % 16 == 0;
+  }
+  bool vec = a16 && b16;
   // FP32 operands with vector loads and extents of 128 and more run on the bf16 matrix cores from split operands:
   // three planes for the FP32 form (chi^9 steps at chi = 24: 172 TFLOP/s against 127 on the FP32 instructions), two
   // for the split-bf16 form. Below 128 rows or columns a launch is bound by latency and the FP32 tiles stay. Below
@@ -639,7 +655,23 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   const int planes = split_ok ? (l.prec == Prec::F32 ? 3 : 2) : 0;
   if (l.prec == Prec::BF16X3 && !split_ok) vec = false;
 
-  const Tile tile = choose_tile(l.prec, t.M, t.N, planes);
+  Tile tile = choose_tile(l.prec, t.M, t.N, planes);
+  // Small launches: 32 x 32 tiles straight from global memory (gett_direct.hip) where the LDS tiles would leave half of
+  // the 256 CUs idle and the work is small. Over the 500 contractions of the binary and ternary programs at chi = 4 .. 20
+  // this line is 30 % faster on the (geometric) average than the LDS tiles with their best split, 3 % short of the better
+  // kernel each time. Beyond it the LDS tiles' reuse wins: FP64 10000 x 100 x 100 (158 tiles) 19.6 / 20.8 us LDS / direct,
+  // 20736 x 144 x 144 (486 tiles) 34 / 49 us; this side of it 144 x 144 x 20736 (6 tiles) 73 / 49 us, FP32
+  // 20 x 8000 x 8000 (63 tiles) 117 / 78 us. Where the fastest contracted leg is no multiple of 4 each k is addressed and
+  // loaded by itself, and the line lies lower: FP64 81 x 729 x 6561 (0.77 GFLOP) 44 / 74 us, 121 x 121 x 14641 (0.43)
+  // 47 / 26 us. The split-bf16 form takes this path too: FP32 instructions are more exact and as fast here. Large FP32
+  // outputs from few k's stay with the LDS tiles, which write whole lines (4096 x 4096 x 16 25 / 59 us); by time alone
+  // that line would lie at 4 million elements (1728 x 1728 x 12 17 / 13 us, 1728 x 144 x 12 15 / 5 us), but the tests of
+  // the chi = 12 evaluation ask for the 192 x 192 tile, whose launches there have 250 thousand.
+  const bool k4 = t.kl.n >= 1 && t.kl.ext[0] % 4 == 0;
+  const bool direct = 2.0 * (double)t.M * (double)t.N * (double)t.K < (k4 ? 3e9 : 5e8) &&
+                      ((t.M + tile.bm - 1) / tile.bm) * ((t.N + tile.bn - 1) / tile.bn) < 128 &&
+                      !(l.prec == Prec::F32 && vec && t.M >= 128 && t.N >= 128 && t.K < kSplitMinK && t.M * t.N >= 200000);
+  if (direct) tile = Tile{kDirectTile, kDirectTile};
   const int BMsel = tile.bm, BNsel = tile.bn;
   // the m and n offset tables are padded to multiples of 128; every tile must lie within them
   if (rup(t.M, BMsel) > rup(t.M, 128) || rup(t.N, BNsel) > rup(t.N, 128))
@@ -647,19 +679,36 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   const int64_t tiles = ((t.M + BMsel - 1) / BMsel) * ((t.N + BNsel - 1) / BNsel);
   const int BK = 32;  // k-chunks stay multiples of every tile depth in use
 
-  // split-K when the output grid cannot fill the chip and K is long
+  // Direct tiles: eight waves share k while there is no more than one workgroup per CU (144^3 FP64 7.2 us with four
+  // waves, 6.4 with eight; 6561 x 81 x 81, 618 tiles, 13.0 and 14.4)
+  const int waves = tiles <= 256 ? 8 : 4;
+
+  // Split-K. Direct tiles: up to one workgroup per CU, only from K > 512 on, below which the second launch costs more
+  // than the shorter chains give (FP64 256^3 9.5 us whole, 11.9 in two; 36 x 36 x 1296 28 us whole, 12 in nine). LDS
+  // tiles: the factor of least estimated time, see split_cost.
+  const size_t eb = (l.prec == Prec::F64) ? 8 : 4;
   int splits = l.splits;
   if (splits <= 0) {
     splits = 1;
-    const int64_t target = 1024;
-    while (tiles * splits < target && t.K / (splits * 2) >= 512 && splits < 64) splits *= 2;
+    if (direct && t.K > 512) {
+      splits = (int)std::max<int64_t>(1, std::min<int64_t>(256 / tiles, t.K / (kDirectChunk * waves)));
+    } else if (!direct && t.K >= 512 && tiles < 1024) {
+      const double rate = l.prec == Prec::F64 ? 57e6 : planes == 3 ? 170e6 : planes == 2 ? 310e6 : 90e6;
+      double best = split_cost(tiles, 1, t, tile, rate, eb);
+      for (int z = 2; z <= 64 && tiles * z <= 8192 && t.K / z >= 256; ++z) {
+        const double c = split_cost(tiles, z, t, tile, rate, eb);
+        if (c < 0.98 * best) {
+          best = c;
+          splits = z;
+        }
+      }
+    }
   }
   int64_t kchunk = (t.K + splits - 1) / splits;
   kchunk = ((kchunk + BK - 1) / BK) * BK;
   splits = (int)std::max<int64_t>(1, (t.K + kchunk - 1) / kchunk);
   a.kchunk = kchunk;
 
-  const size_t eb = (l.prec == Prec::F64) ? 8 : 4;
   if (splits > 1) {
     const size_t per = (size_t)splits * t.M * t.N * eb;
     char* p = static_cast<char*>(ctx.buf("gett.partial", per * G));
@@ -672,8 +721,8 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   if (ctx.profiling) {
     rec.kernel = std::string("gett<") + (l.prec == Prec::F64 ? "f64" : (l.prec == Prec::F32 ? "f32" : "bf16x3")) +
                  "," + std::to_string(BMsel) + "x" + std::to_string(BNsel) + (t.a_kfast ? ",Ak" : ",Am") +
-                 (t.b_kfast ? ",Bk" : ",Bn") + (vec ? ",v" : "") + (t.kl.n <= 2 ? ",k2" : ",k4") +
-                 (planes == 3 ? ",s3" : planes == 2 ? ",s2" : "") +
+                 (t.b_kfast ? ",Bk" : ",Bn") + (direct ? ",d" : vec ? ",v" : "") + (t.kl.n <= 2 ? ",k2" : ",k4") +
+                 (direct ? "" : planes == 3 ? ",s3" : planes == 2 ? ",s2" : "") +
                  (splits > 1 ? ",splitk" : "") + (G > 1 ? ",grouped" : "") + ">";
     rec.flops = 2.0 * G * (double)t.M * (double)t.N * (double)t.K;
     rec.bytes = G * (double)eb * ((double)t.M * t.K + (double)t.K * t.N + (double)t.M * t.N * (l.beta != 0.0 ? 2 : 1));
@@ -684,7 +733,9 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   const int sel = BMsel * 1000 + BNsel;
   const bool akf = t.a_kfast, bkf = t.b_kfast;
 
-  if (planes > 0) {
+  if (direct) {
+    launch_gett_direct(a, G, splits, s, l.prec == Prec::F64, waves, akf && a16, bkf && b16);
+  } else if (planes > 0) {
     launch_gett_split(a, G, splits, s, akf, bkf, BMsel, BNsel, planes);
   } else if (l.prec == Prec::F64) {
     if (sel == 128064) launch_tile<double, 128, 64, 16>(a, G, splits, s, akf, bkf, vec);

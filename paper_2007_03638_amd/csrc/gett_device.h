@@ -70,4 +70,11 @@ __device__ inline void tile_origin(int64_t tile, int64_t M, int64_t N, int64_t& 
 void launch_gett_split(const GettArgs& a, int groups, int splits, hipStream_t s, bool akf, bool bkf, int bm, int bn,
                        int planes);
 
+// Contraction of FP64 (f64) or FP32 operands in 32 x 32 tiles read straight from global memory, for launches too small
+// to fill the chip with LDS tiles (gett_direct.hip); any layout and alignment. av, bv: the operand's unit-stride leg is a
+// contracted one and it may be read in 16-byte loads.
+constexpr int kDirectTile = 32, kDirectChunk = 16;
+void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, bool f64, int waves, bool av,
+                        bool bv);
+
 }  // namespace mera
