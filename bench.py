@@ -126,7 +126,7 @@ def counter_traffic(kernel_variant):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter summaries, or None when the
     kernel's source changed since the counters were taken or no summary covers the variant."""
     import hashlib
-    for summary, source in (("gett_f32_chi24_counters.md", "gett.hip"), ("gett_split_chi24_counters.md", "gett_split.hip")):
+    for summary, source in (("gett_f32_chi24_counters.md", "gett.hip"), ("gett_split_chi24_counters.md", "gett_split_device.h")):
         path = os.path.join(ROOT, "profiles", summary)
         src = os.path.join(ROOT, "paper_2007_03638_amd", "csrc", source)
         if not os.path.exists(path):

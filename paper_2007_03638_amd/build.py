@@ -12,8 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmera_hip.so")
 ROOT = os.path.dirname(HERE)
 
-SOURCES = ["gett_split.hip", "gett.hip", "gett_direct.hip", "vec.hip", "noalloc.hip", "network.cpp", "linalg.cpp", "model.cpp", "mera.cpp", "optim.cpp",
-           "server.cpp", "capi.cpp"]
+SOURCES = ["gett_split.hip", "gett_split_scalar.hip", "gett.hip", "gett_direct.hip", "vec.hip", "noalloc.hip",
+           "network.cpp", "linalg.cpp", "model.cpp", "mera.cpp", "optim.cpp", "server.cpp", "capi.cpp"]
 
 HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(256, 2) gett_kernel(Args g) {
 }
 
 // ---- split-bf16 (hi + lo) form with scalar loads: C ~= A_hi B_hi + A_hi B_lo + A_lo B_hi on the bf16 MFMA (operands
-// that allow 16-byte loads run on gett_split.hip where both extents reach 128) -----------------------------------
+// of 128 and more in both extents run on gett_split_device.h) -----------------------------------------------------
 
 __device__ inline void split_bf16(float x, __bf16& hi, __bf16& lo) {
   hi = (__bf16)x;
@@ -575,13 +575,14 @@ int64_t rup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // occupancy). FP32 matrix instructions: among 192 x 192, 128 x 192, 192 x 128 and 128 x 128 the one with the least
 // padding, ties to the larger tile; chi^2 = 576 and chi^4 extents at chi = 24 are multiples of 192 but not of 128.
 // The split kernels (`planes` > 0) the same, the FP32 form (three planes) without the 192 x 192 tile, whose second
-// sums and fragments do not fit the registers (spilling, it ran 159 TFLOP/s against 171 with 128 x 192). A 192-row (column) tile is only chosen when it pads no more than a
-// 128-row one, so the offset tables, padded to multiples of 128, cover every tile. Split-bf16 with scalar loads: at
-// most 128 x 128. 64-wide tiles for extents below 128.
-Tile choose_tile(Prec p, int64_t M, int64_t N, int planes) {
+// sums and fragments do not fit the registers (spilling, it ran 159 TFLOP/s against 171 with 128 x 192), and with
+// 128 x 128 only (`only128`) where an operand is walked along k without 16-byte loads. A 192-row (column) tile is only
+// chosen when it pads no more than a 128-row one, so the offset tables, padded to multiples of 128, cover every tile.
+// Split-bf16 with 64-wide tiles: scalar loads. 64-wide tiles for extents below 128.
+Tile choose_tile(Prec p, int64_t M, int64_t N, int planes, bool only128) {
   const bool bigm = M >= 128, bign = N >= 128;
   if (p == Prec::F64) return Tile{bigm ? 128 : 64, 64};
-  if ((p == Prec::BF16X3 && planes == 0) || !bigm || !bign) return Tile{bigm ? 128 : 64, bign ? 128 : 64};
+  if ((p == Prec::BF16X3 && planes == 0) || !bigm || !bign || only128) return Tile{bigm ? 128 : 64, bign ? 128 : 64};
   const Tile cand[4] = {{192, 192}, {128, 192}, {192, 128}, {128, 128}};
   Tile best = cand[3];
   double best_pad = 1e300;
@@ -642,32 +643,33 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
     b16 = b16 && (uintptr_t)l.B[g] % 16 == 0;
   }
   bool vec = a16 && b16;
-  // FP32 operands with vector loads and extents of 128 and more run on the bf16 matrix cores from split operands:
-  // three planes for the FP32 form (chi^9 steps at chi = 24: 172 TFLOP/s against 127 on the FP32 instructions), two
-  // for the split-bf16 form. Below 128 rows or columns a launch is bound by latency and the FP32 tiles stay. Below
-  // kSplitMinK a step is bound by writing C and both are alike (ternary maps at chi = 16 .. 32, whose composites have
-  // K = chi: 739 / 731, 3537 / 3507, 9803 / 9795, 86792 / 87555 us native / split): the FP32 instructions stay, whose
-  // 192 x 192 tile reads less. A row-walking operand's pair of k's must not straddle two values of the next
-  // contracted leg: even extent.
+  // FP32 operands with extents of 128 and more run on the bf16 matrix cores from split operands: three planes for the
+  // FP32 form (chi^9 steps at chi = 24: 172 TFLOP/s against 127 on the FP32 instructions), two for the split-bf16 form.
+  // Below 128 rows or columns a launch is bound by latency and the FP32 tiles stay. Below kSplitMinK a step is bound by
+  // writing C and both are alike (ternary maps at chi = 16 .. 32, whose composites have K = chi: 739 / 731, 3537 / 3507,
+  // 9803 / 9795, 86792 / 87555 us native / split): the FP32 instructions stay, whose 192 x 192 tile reads less. With
+  // vector loads a row-walking operand's pair of k's must not straddle two values of the next contracted leg: even
+  // extent; every other layout (chi not a multiple of 4) is loaded by elements.
   constexpr int64_t kSplitMinK = 64;
-  const bool split_ok = vec && t.M >= 128 && t.N >= 128 && t.kl.n >= 1 && t.kl.ext[0] % 2 == 0 &&
-                        (l.prec == Prec::BF16X3 || (l.prec == Prec::F32 && t.K >= kSplitMinK));
-  const int planes = split_ok ? (l.prec == Prec::F32 ? 3 : 2) : 0;
-  if (l.prec == Prec::BF16X3 && !split_ok) vec = false;
+  const bool split_form = t.M >= 128 && t.N >= 128 &&
+                          (l.prec == Prec::BF16X3 || (l.prec == Prec::F32 && t.K >= kSplitMinK));
+  const int planes = !split_form ? 0 : l.prec == Prec::F32 ? 3 : 2;
+  if (planes > 0) vec = vec && t.kl.n >= 1 && t.kl.ext[0] % 2 == 0;
+  else if (l.prec == Prec::BF16X3) vec = false;
 
-  Tile tile = choose_tile(l.prec, t.M, t.N, planes);
+  Tile tile = choose_tile(l.prec, t.M, t.N, planes, planes == 3 && !vec && (t.a_kfast || t.b_kfast));
   // Small launches: 32 x 32 tiles straight from global memory (gett_direct.hip) where the LDS tiles would leave half of
   // the 256 CUs idle and the work is small. Over the 500 contractions of the binary and ternary programs at chi = 4 .. 20
   // this line is 30 % faster on the (geometric) average than the LDS tiles with their best split, 3 % short of the better
   // kernel each time. Beyond it the LDS tiles' reuse wins: FP64 10000 x 100 x 100 (158 tiles) 19.6 / 20.8 us LDS / direct,
   // 20736 x 144 x 144 (486 tiles) 34 / 49 us; this side of it 144 x 144 x 20736 (6 tiles) 73 / 49 us, FP32
-  // 20 x 8000 x 8000 (63 tiles) 117 / 78 us. Where the fastest contracted leg is no multiple of 4 each k is addressed and
-  // loaded by itself, and the line lies lower: FP64 81 x 729 x 6561 (0.77 GFLOP) 44 / 74 us, 121 x 121 x 14641 (0.43)
-  // 47 / 26 us. The split-bf16 form takes this path too: FP32 instructions are more exact and as fast here. Large FP32
-  // outputs from few k's stay with the LDS tiles, which write whole lines (4096 x 4096 x 16 25 / 59 us); by time alone
-  // that line would lie at 4 million elements (1728 x 1728 x 12 17 / 13 us, 1728 x 144 x 12 15 / 5 us), but the tests of
-  // the chi = 12 evaluation ask for the 192 x 192 tile, whose launches there have 250 thousand.
-  const bool k4 = t.kl.n >= 1 && t.kl.ext[0] % 4 == 0;
+  // 20 x 8000 x 8000 (63 tiles) 117 / 78 us. Where each k is loaded by itself (the fastest contracted leg no multiple
+  // of 4, or a k-walking operand without 16-byte loads) the line lies lower: FP64 81 x 729 x 6561 (0.77 GFLOP) 44 / 74 us,
+  // 121 x 121 x 14641 (0.43) 47 / 26 us. Large FP32 outputs from few k's stay with the LDS tiles, which write whole
+  // lines (4096 x 4096 x 16 25 / 59 us); by time alone that line would lie at 4 million elements (1728 x 1728 x 12
+  // 17 / 13 us, 1728 x 144 x 12 15 / 5 us), but the tests of the chi = 12 evaluation ask for the 192 x 192 tile, whose
+  // launches there have 250 thousand.
+  const bool k4 = t.kl.n >= 1 && t.kl.ext[0] % 4 == 0 && (a16 || !t.a_kfast) && (b16 || !t.b_kfast);
   const bool direct = 2.0 * (double)t.M * (double)t.N * (double)t.K < (k4 ? 3e9 : 5e8) &&
                       ((t.M + tile.bm - 1) / tile.bm) * ((t.N + tile.bn - 1) / tile.bn) < 128 &&
                       !(l.prec == Prec::F32 && vec && t.M >= 128 && t.N >= 128 && t.K < kSplitMinK && t.M * t.N >= 200000);
@@ -734,9 +736,9 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   const bool akf = t.a_kfast, bkf = t.b_kfast;
 
   if (direct) {
-    launch_gett_direct(a, G, splits, s, l.prec == Prec::F64, waves, akf && a16, bkf && b16);
+    launch_gett_direct(a, G, splits, s, l.prec, waves, akf && a16, bkf && b16);
   } else if (planes > 0) {
-    launch_gett_split(a, G, splits, s, akf, bkf, BMsel, BNsel, planes);
+    (vec ? launch_gett_split : launch_gett_split_scalar)(a, G, splits, s, akf, bkf, BMsel, BNsel, planes);
   } else if (l.prec == Prec::F64) {
     if (sel == 128064) launch_tile<double, 128, 64, 16>(a, G, splits, s, akf, bkf, vec);
     else launch_tile<double, 64, 64, 16>(a, G, splits, s, akf, bkf, vec);
@@ -752,7 +754,6 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
     }
   } else {
     switch (sel) {
-      case 128128: launch_bf16x3<128, 128, 32>(a, G, splits, s, akf, bkf); break;
       case 128064: launch_bf16x3<128, 64, 32>(a, G, splits, s, akf, bkf); break;
       case 64128: launch_bf16x3<64, 128, 32>(a, G, splits, s, akf, bkf); break;
       default: launch_bf16x3<64, 64, 32>(a, G, splits, s, akf, bkf); break;

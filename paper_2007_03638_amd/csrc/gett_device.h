@@ -64,17 +64,19 @@ __device__ inline void tile_origin(int64_t tile, int64_t M, int64_t N, int64_t& 
   n0 = (mgroups ? small : big) * BN;
 }
 
-// FP32 contraction on the bf16 matrix cores from split operands (gett_split.hip): planes = 3 (FP32 form) or
-// 2 (split-bf16 form); tile bm x bn with bm, bn in {128, 192}. The operands must allow 16-byte loads and the fastest
-// contracted leg's extent must be even.
+// FP32 contraction on the bf16 matrix cores from split operands (gett_split_device.h): planes = 3 (FP32 form) or
+// 2 (split-bf16 form); tile bm x bn with bm, bn in {128, 192}. The first needs operands that allow 16-byte loads and an
+// even extent of the fastest contracted leg, the second takes any layout.
 void launch_gett_split(const GettArgs& a, int groups, int splits, hipStream_t s, bool akf, bool bkf, int bm, int bn,
                        int planes);
+void launch_gett_split_scalar(const GettArgs& a, int groups, int splits, hipStream_t s, bool akf, bool bkf, int bm,
+                              int bn, int planes);
 
-// Contraction of FP64 (f64) or FP32 operands in 32 x 32 tiles read straight from global memory, for launches too small
-// to fill the chip with LDS tiles (gett_direct.hip); any layout and alignment. av, bv: the operand's unit-stride leg is a
-// contracted one and it may be read in 16-byte loads.
+// Contraction in 32 x 32 tiles read straight from global memory, for launches too small to fill the chip with LDS tiles
+// (gett_direct.hip); any layout and alignment. av, bv: the operand's unit-stride leg is a contracted one and it may be
+// read in 16-byte loads.
 constexpr int kDirectTile = 32, kDirectChunk = 16;
-void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, bool f64, int waves, bool av,
+void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, Prec prec, int waves, bool av,
                         bool bv);
 
 }  // namespace mera

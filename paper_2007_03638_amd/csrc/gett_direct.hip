@@ -55,9 +55,19 @@ __device__ inline void load4(T (&out)[4], const T* p, uint32_t stride) {
   }
 }
 
-// K4: the fastest contracted leg's extent is a multiple of 4, so that four consecutive k's differ in that leg only and
-// take one offset. AV, BV (only with K4): that leg is the operand's unit-stride one and its addresses are 16-byte aligned.
-template <typename T, int NKL, int WAVES, bool K4, bool AV, bool BV>
+template <bool SPLIT, typename T>
+__device__ inline T operand(T x) {
+  if constexpr (SPLIT) {
+    const float hi = (float)(__bf16)x;
+    return hi + (float)(__bf16)(x - hi);
+  }
+  return x;
+}
+
+// AV, BV: the operand's unit-stride leg is the fastest contracted one, its extent a multiple of 4, and its addresses are
+// 16-byte aligned, so that four consecutive k's are read at once.
+// SPLIT: the split-bf16 form; each operand element is replaced by the sum of the two bf16 numbers it is split into.
+template <typename T, int NKL, int WAVES, bool AV, bool BV, bool SPLIT>
 __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
   using F = Mma16<T>;
   __shared__ T red[WAVES][TILE][TILE + 1];
@@ -98,14 +108,14 @@ __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = T(0);
 
-  // Within a chunk lane group kq takes the k's 4 kq .. 4 kq + 3, one per matrix instruction: the order of the k's in an
-  // instruction is free as long as both operands follow it, and a row's four are one load where k is the fast leg.
+  // Matrix instruction s of a chunk takes the k's 4 s + kq, in ascending order. With vector loads lane group kq takes
+  // 4 kq + s instead: the order is free as long as both operands follow it, and a row's four k's are one load.
   static_assert(CHUNK == 16, "four lane groups of four k's");
+  constexpr bool V = AV || BV;
   T av[2][2][4], bv[2][2][4];  // two chunks: one multiplied, the next one on its way
   auto load = [&](int slot, int64_t k) {
-    const int64_t kk = k + 4 * kq;
-    if constexpr (K4) {  // ke is a multiple of 4 then
-      const uint32_t kc = (uint32_t)(kk < ke ? kk : ke - 4);
+    if constexpr (V) {  // ke is a multiple of 4 then
+      const uint32_t kc = (uint32_t)(k + 4 * kq < ke ? k + 4 * kq : ke - 4);
       const uint64_t oa = k_offset<NKL>(kc, g.kl, g.kl.sa), ob = k_offset<NKL>(kc, g.kl, g.kl.sb);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -115,7 +125,7 @@ __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const uint32_t kc = (uint32_t)(kk + s < ke ? kk + s : ke - 1);
+        const uint32_t kc = (uint32_t)(k + 4 * s + kq < ke ? k + 4 * s + kq : ke - 1);
         const uint64_t oa = k_offset<NKL>(kc, g.kl, g.kl.sa), ob = k_offset<NKL>(kc, g.kl, g.kl.sb);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -128,12 +138,12 @@ __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
   auto mul = [&](int slot, int64_t k) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const bool in = k + 4 * kq + s < ke;
+      const bool in = k + (V ? 4 * kq + s : 4 * s + kq) < ke;
       T x[2], y[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        x[i] = in ? av[slot][i][s] : T(0);
-        y[i] = in ? bv[slot][i][s] : T(0);
+        x[i] = in ? operand<SPLIT>(av[slot][i][s]) : T(0);
+        y[i] = in ? operand<SPLIT>(bv[slot][i][s]) : T(0);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -172,35 +182,37 @@ __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
   }
 }
 
-template <typename T, int NKL, int WAVES>
-void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, bool k4, bool av, bool bv) {
+template <typename T, int NKL, int WAVES, bool SPLIT>
+void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, bool av, bool bv) {
   const dim3 block(64 * WAVES);
-  if (!k4) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, false, false, false>), grid, block, 0, s, a);
-  else if (av && bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, true, true>), grid, block, 0, s, a);
-  else if (av) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, true, false>), grid, block, 0, s, a);
-  else if (bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, false, true>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, false, false>), grid, block, 0, s, a);
+  if (av && bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, true, SPLIT>), grid, block, 0, s, a);
+  else if (av) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, false, SPLIT>), grid, block, 0, s, a);
+  else if (bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, false, true, SPLIT>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, false, false, SPLIT>), grid, block, 0, s, a);
 }
 
-template <typename T>
-void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, int waves, bool k4, bool av, bool bv) {
+template <typename T, bool SPLIT>
+void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, int waves, bool av, bool bv) {
   if (waves == 8) {
-    if (a.kl.n <= 2) launch_direct<T, 2, 8>(a, grid, s, k4, av, bv);
-    else launch_direct<T, 4, 8>(a, grid, s, k4, av, bv);
+    if (a.kl.n <= 2) launch_direct<T, 2, 8, SPLIT>(a, grid, s, av, bv);
+    else launch_direct<T, 4, 8, SPLIT>(a, grid, s, av, bv);
   } else {
-    if (a.kl.n <= 2) launch_direct<T, 2, 4>(a, grid, s, k4, av, bv);
-    else launch_direct<T, 4, 4>(a, grid, s, k4, av, bv);
+    if (a.kl.n <= 2) launch_direct<T, 2, 4, SPLIT>(a, grid, s, av, bv);
+    else launch_direct<T, 4, 4, SPLIT>(a, grid, s, av, bv);
   }
 }
 
 }  // namespace
 
-void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, bool f64, int waves, bool av, bool bv) {
+void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, Prec prec, int waves, bool av, bool bv) {
   const int64_t tiles = ((a.M + TILE - 1) / TILE) * ((a.N + TILE - 1) / TILE);
   const dim3 grid((unsigned)tiles, (unsigned)groups, (unsigned)splits);
   const bool k4 = a.kl.n >= 1 && a.kl.ext[0] % 4 == 0;
-  if (f64) launch_direct<double>(a, grid, s, waves, k4, av, bv);
-  else launch_direct<float>(a, grid, s, waves, k4, av, bv);
+  av = av && k4;
+  bv = bv && k4;
+  if (prec == Prec::F64) launch_direct<double, false>(a, grid, s, waves, av, bv);
+  else if (prec == Prec::F32) launch_direct<float, false>(a, grid, s, waves, av, bv);
+  else launch_direct<float, true>(a, grid, s, waves, av, bv);
 }
 
 }  // namespace mera

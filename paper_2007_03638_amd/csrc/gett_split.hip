@@ -1,422 +1,11 @@
-// GETT on the bf16 matrix cores with FP32 operands split into bf16 planes when a tile is staged.
-//
-// planes = 3 (the FP32 form): x = hi + mid + lo with hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid, which is
-// exact for every finite x below 3.39e38 whose low part is no denormal (8 significant bits each, 24 in all; both
-// subtractions are exact). A product a b is formed as the six plane products of relative weight down to 2^-18,
-//   lo_a hi_b + hi_a lo_b + mid_a mid_b + mid_a hi_b + hi_a mid_b + hi_a hi_b,
-// each exact in the matrix core, smallest first, into sums that start from zero for every 16 k's and are then added to
-// the FP32 accumulators by vector additions. What is left out (mid lo, lo mid, lo lo) is below 2^-26 of |a b|, a
-// quarter of the FP32 rounding of a single product. The fresh sums matter: a bf16 matrix instruction adds 8 products
-// to its accumulator at a time, cut (towards minus infinity) at 2^-26 of the largest of them, so that products added
-// straight to a long sum lose their low bits and leave a bias; measured over K = 13824, error against 64 bits 1.9e-6
-// that way, 5.8e-7 with fresh sums and 2.2e-6 on the FP32 matrix instructions (K = 576: 3.8e-7, 1.3e-7, 4.5e-7). What
-// bias the cut leaves within 16 k's is turned round in every other tile, of which one operand is staged negated and the
-// sums subtracted (over K = 331776 of random signs it had been a third of the error).
-// planes = 2 (the split-bf16 form): x ~ hi + lo, products lo hi, hi lo, hi hi.
-//
-// What bounds it: the bf16 matrix cores and the power they draw. 2.5 PFLOP/s / 6 = 417 TFLOP/s of contraction arithmetic in the FP32 form
-// against 157 TFLOP/s on the FP32 matrix instructions; 833 in the split-bf16 form. At full load the card lowers its
-// clock (1.7 GHz measured on the chi^9 steps at chi = 24, where the matrix cores are busy 0.60-0.63 of the time): a
-// large bf16 library product reaches 1405 TFLOP/s on it, i.e. 234 and 468 per plane product. Measured: FP32 form 172
-// TFLOP/s with 128 x 192 tiles (127 before, on the FP32 instructions with 192 x 192), split-bf16 form 310-322 with
-// 192 x 192 tiles (221 before with 128 x 128 tiles and one barrier per 32 k's).
-//
-// Tile and waves: 4 waves of 64 x 64 to 96 x 96, two workgroups per CU (LDS up to 77 KB of 160), so that one's
-// prologue, epilogue and waits hide behind the other's matrix instructions. Per 32 x 32 block and 16 k's: 6 (3) matrix
-// instructions, 16 additions (FP32 form), and a share of the fragment reads, splitting, staging and loads, all spread
-// over the blocks (slots) of the tile.
-#include <algorithm>
-#include <type_traits>
-
-#include "gett_device.h"
+// Instances of the split-operand GETT kernels (gett_split_device.h) with 16-byte loads.
+#include "gett_split_device.h"
 
 namespace mera {
 
-namespace {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int BK = 16;  // one bf16 matrix instruction (32 x 32 x 16) deep
-
-// Two values as NP packed pairs of bf16 planes (value 0 in the low half), rounded to nearest even: one packed
-// conversion per plane, and the residuals x - plane (exact) as two-element dot products with (-1, 0) and (0, -1),
-// which need no unpacking. The two constants come through an empty asm statement: as a literal the compiler encodes
-// (-1, 0) as the inline constant -1.0, which this instruction reads as the FP32 pattern, i.e. as (0, -1).
-template <int NP>
-__device__ inline void split_pair(float x0, float x1, uint32_t (&out)[NP]) {
-  uint32_t m0 = 0x0000bf80u, m1 = 0xbf800000u;
-  __asm__("" : "+s"(m0));
-  __asm__("" : "+s"(m1));
-#pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    const bf16x2 w{(__bf16)x0, (__bf16)x1};
-    out[p] = __builtin_bit_cast(uint32_t, w);
-    if (p + 1 < NP) {
-      x0 = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, m0), x0, false);
-      x1 = __builtin_amdgcn_fdot2_f32_bf16(w, __builtin_bit_cast(bf16x2, m1), x1, false);
-    }
-  }
-}
-
-// LDS image of one operand's tile: NP planes, each two halves of 8 k's, each half R rows of 8 bf16 (16 bytes). A
-// fragment of the matrix instruction (row = lane % 32, k half = lane / 32) is then one 16-byte read per lane, 32
-// lanes in 512 contiguous bytes. The gap between the halves spreads the staging writes over the banks: a k-walking
-// operand's 32 lanes write 8 bytes to 8 rows in each half (gap 32 dwords), a row-walking one's write 4 bytes to
-// every fourth row, 4 k pairs in each half (gap 8 dwords).
-template <bool KF, int R, int NP>
-struct Image {
-  static constexpr int HALF = R * 8 + (KF ? 64 : 16);
-  static constexpr int PLANE = 2 * HALF;
-  static constexpr int SIZE = NP * PLANE;
-};
-
-// Loads one operand's R x 16 tile into registers and stages it split into the LDS image, by 128 threads (two
-// waves; the other two load the other operand). 16-byte loads along the operand's unit-stride leg: 4 k's of
-// one row (KF), or the same 4 rows at two neighbouring k's, which differ in the fastest contracted leg only (its
-// extent is even). Rows past the extent read padded table entries (offset 0) and feed accumulator rows that are
-// never stored; k's past the end are clamped for the address and zeroed when staged, in the last tile only.
-template <bool KF, int R, int NKL, int NP>
-struct SplitLoader {
-  static constexpr int U = KF ? R / 32 : R / 64;
-  static constexpr int NV = KF ? U : 2 * U;
-  typedef Image<KF, R, NP> Im;
-  const float* rowp[U];
-  int r0, k0;
-  f32x4 reg[NV];
-
-  __device__ inline void init(const float* base, const int64_t* off_r, int64_t rbase, int t) {
-    r0 = KF ? t / 4 : 4 * (t / 8);
-    k0 = KF ? 4 * (t % 4) : 2 * (t % 8);
-#pragma unroll
-    for (int i = 0; i < U; ++i) rowp[i] = base + off_r[rbase + r0 + (KF ? 32 : 64) * i];
-  }
-  __device__ inline uint64_t offset(int64_t kt, int64_t K, const GettKLegs& kl, const uint32_t* stride) const {
-    const uint32_t k = (uint32_t)kt + (uint32_t)k0, klast = (uint32_t)K - (KF ? 4 : 2);
-    return k_offset<NKL>(k < klast ? k : klast, kl, stride);
-  }
-  __device__ inline void load_unit(int i, uint64_t o, const uint32_t* stride) {
-    if (KF) {
-      reg[i] = *reinterpret_cast<const f32x4*>(rowp[i] + o);
-    } else {
-      reg[2 * i] = *reinterpret_cast<const f32x4*>(rowp[i] + o);
-      reg[2 * i + 1] = *reinterpret_cast<const f32x4*>(rowp[i] + o + stride[0]);
-    }
-  }
-  __device__ inline void load(int64_t kt, int64_t K, const GettKLegs& kl, const uint32_t* stride) {
-    const uint64_t o = offset(kt, K, kl, stride);
-#pragma unroll
-    for (int i = 0; i < U; ++i) load_unit(i, o, stride);
-  }
-  // Staging in pieces of two pairs per thread: a k-walking operand's vector (8 bytes per plane), or two of the four
-  // rows of a row-walking one (4 bytes per row and plane). `cut`: write zeros (k past the end; K is a multiple of a
-  // vector's or pair's length, so it is all or nothing).
-  static constexpr int PIECES = KF ? U : 2 * U;
-  __device__ inline __bf16* at(__bf16* lds) const { return lds + (k0 >> 3) * Im::HALF + r0 * 8 + (k0 & 7); }
-  // `flip`: XORed into the sign bits (0, or 0x80000000 to stage the negative)
-  template <bool FLIP>
-  __device__ inline void stage_piece(int q, __bf16* dst, bool cut, uint32_t flip) const {
-    auto val = [&](float v) { return FLIP ? __uint_as_float(__float_as_uint(v) ^ flip) : v; };
-    uint32_t a[NP], b[NP];
-    if (KF) {
-      f32x4 x = reg[q];
-      if (cut) x = f32x4{0.f, 0.f, 0.f, 0.f};
-      split_pair<NP>(val(x[0]), val(x[1]), a);
-      split_pair<NP>(val(x[2]), val(x[3]), b);
-#pragma unroll
-      for (int p = 0; p < NP; ++p) *reinterpret_cast<u32x2*>(dst + p * Im::PLANE + q * 32 * 8) = u32x2{a[p], b[p]};
-    } else {
-      const int i = q >> 1, j = 2 * (q & 1);
-      f32x4 x = reg[2 * i], y = reg[2 * i + 1];
-      if (cut) x = y = f32x4{0.f, 0.f, 0.f, 0.f};
-      split_pair<NP>(val(x[j]), val(y[j]), a);
-      split_pair<NP>(val(x[j + 1]), val(y[j + 1]), b);
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        *reinterpret_cast<uint32_t*>(dst + p * Im::PLANE + (i * 64 + j) * 8) = a[p];
-        *reinterpret_cast<uint32_t*>(dst + p * Im::PLANE + (i * 64 + j + 1) * 8) = b[p];
-      }
-    }
-  }
-  // whether piece q is the last that reads its unit's registers, and that unit
-  static constexpr bool frees(int q) { return KF || (q & 1); }
-  static constexpr int unit_of(int q) { return KF ? q : q >> 1; }
-};
-
-// Elements of a wave's tile by FP32 multiply-adds over k, for a wave whose split products gave a NaN: an infinite
-// element (or one that bf16 rounds to infinity) splits into inf - inf, where FP32 arithmetic may give an infinity or
-// a number. Writes partial sums or C as the normal epilogue does.
-template <int NKL>
-__device__ inline void plain_wave_tile(const GettArgs& g, int grp, int64_t r0, int64_t c0, int rows, int cols,
-                                             int64_t kb, int64_t ke, int lane) {
-  const float* A = static_cast<const float*>(g.A[grp]);
-  const float* B = static_cast<const float*>(g.B[grp]);
-  for (int e = lane; e < rows * cols; e += 64) {
-    const int64_t row = r0 + e / cols, col = c0 + e % cols;
-    if (row >= g.M || col >= g.N) continue;
-    const float* a = A + g.a_m[row];
-    const float* b = B + g.b_n[col];
-    float s = 0.f;
-    for (int64_t k = kb; k < ke && s == s; ++k)
-      s = fmaf(a[k_offset<NKL>((uint32_t)k, g.kl, g.kl.sa)], b[k_offset<NKL>((uint32_t)k, g.kl, g.kl.sb)], s);
-    if (g.split) {
-      (static_cast<float*>(g.partial[grp]) + (int64_t)blockIdx.z * g.M * g.N)[row * g.N + col] = s;
-    } else {
-      float* c = static_cast<float*>(g.C[grp]) + g.c_m[row] + g.c_n[col];
-      const float v = float(g.alpha) * s;
-      *c = g.beta != 0.0 ? v + float(g.beta) * *c : v;
-    }
-  }
-}
-
-template <int BM, int BN, bool AKF, bool BKF, int NKL, int NP>
-__global__ void __launch_bounds__(256, 2) gett_split_kernel(GettArgs g) {
-  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
-  typedef Image<AKF, BM, NP> ImA;
-  typedef Image<BKF, BN, NP> ImB;
-  __shared__ __attribute__((aligned(16))) __bf16 As[2][ImA::SIZE];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][ImB::SIZE];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = (wave >> 1) * WM;
-  const int wn = (wave & 1) * WN;
-  int64_t m0, n0;
-  tile_origin<BM, BN>(xcd_tile(blockIdx.x, gridDim.x), g.M, g.N, m0, n0);
-  const int64_t kb = (int64_t)blockIdx.z * g.kchunk;
-  const int64_t ke = (g.K < kb + g.kchunk) ? g.K : kb + g.kchunk;
-  const int grp = blockIdx.y;
-
-  f32x16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // plane products, smallest first: (plane of A, plane of B)
-  constexpr int NQ = NP == 3 ? 6 : 3;
-  constexpr int QA[6] = {NP == 3 ? 2 : 1, 0, NP == 3 ? 1 : 0, 1, 0, 0};
-  constexpr int QB[6] = {0, NP == 3 ? 2 : 1, NP == 3 ? 1 : 0, 0, 1, 0};
-
-  // Wave tile in slots, one 32 x 32 block each, the blocks of a row one after another (of a column where the tile is
-  // taller than wide). Fragments of the first block of a tile are read behind the barrier of the tile before; the
-  // others two slots ahead of their use.
-  constexpr bool ROWS = FM <= FN;                       // outer loop over block rows
-  constexpr int NO = ROWS ? FM : FN, NI = ROWS ? FN : FM;
-  constexpr int S = NO * NI;
-  const int fo = ROWS ? (lane >> 5) * ImA::HALF + (wm + (lane & 31)) * 8 : (lane >> 5) * ImB::HALF + (wn + (lane & 31)) * 8;
-  const int fi = ROWS ? (lane >> 5) * ImB::HALF + (wn + (lane & 31)) * 8 : (lane >> 5) * ImA::HALF + (wm + (lane & 31)) * 8;
-  constexpr int PO = ROWS ? ImA::PLANE : ImB::PLANE, PI = ROWS ? ImB::PLANE : ImA::PLANE;
-  constexpr int RO = NO == 3 ? 3 : 2;                    // the next tile's first fragments may not replace the last row's
-  bf16x8 fro[RO][NP], fri[NI][NP];
-  auto read_o = [&](int buf, int o) {
-    const __bf16* at = (ROWS ? As[buf] : Bs[buf]) + fo + o * 32 * 8;
-#pragma unroll
-    for (int p = NP - 1; p >= 0; --p) fro[o % RO][p] = *reinterpret_cast<const bf16x8*>(at + p * PO);
-  };
-  auto read_i = [&](int buf, int i) {
-    const __bf16* at = (ROWS ? Bs[buf] : As[buf]) + fi + i * 32 * 8;
-#pragma unroll
-    for (int p = NP - 1; p >= 0; --p) fri[i][p] = *reinterpret_cast<const bf16x8*>(at + p * PI);
-  };
-  static_assert(NP == 2 || S % 2 == 0, "slot 0 must not reuse the last slot's sums");
-  f32x16 part[2] = {};
-  auto multiply = [&](int s) {
-    const int o = s / NI, i = s % NI;
-    f32x16& c = acc[ROWS ? o : i][ROWS ? i : o];
-    f32x16 t = NP == 3 ? f32x16{} : c;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const bf16x8 a = ROWS ? fro[o % RO][QA[q]] : fri[i][QA[q]];
-      const bf16x8 b = ROWS ? fri[i][QB[q]] : fro[o % RO][QB[q]];
-      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, t, 0, 0, 0);
-    }
-    if (NP == 3) part[s & 1] = t;
-    else c = t;
-  };
-  // adds the sums of block s of a tile staged with this sign
-  auto flush = [&](int s, float sign) {
-    if (NP == 3) {
-      const int o = s / NI, i = s % NI;
-      acc[ROWS ? o : i][ROWS ? i : o] += sign * part[s & 1];
-    }
-  };
-
-  // One tile t (one barrier, before the last slot): the matrix instructions read it from LDS buffer t & 1, while
-  // tile t + 1, in registers since tile t - 1, is split and staged into the other buffer piece by piece over the
-  // slots before the barrier (TAIL: with zeros past the end), each unit of registers being reloaded from tile t + 2
-  // as soon as it is staged, so that a load has about a tile's time. Every wave runs the same number of barriers.
-  // In the FP32 form one operand's odd tiles are staged negated (FLIP: by this wave): the one with fewer rows, so that
-  // neither team has much more to do than the other (with 192 x 128 tiles: chi^9 step 29.6 ms against 33.2).
-  auto tile = [&](auto tail_tag, auto flip_tag, auto& ld, int64_t kt, int buf, __bf16* lds, const uint32_t* stride) {
-    constexpr bool TAIL = decltype(tail_tag)::value;
-    constexpr bool FLIP = NP == 3 && decltype(flip_tag)::value;
-    typedef std::remove_reference_t<decltype(ld)> L;
-    const uint64_t off = ld.offset(kt + 2 * BK, g.K, g.kl, stride);
-    const bool cut = TAIL && kt + BK + ld.k0 >= ke;
-    __bf16* const at = ld.at(lds + (buf ^ 1) * L::Im::SIZE);
-    const float sign = buf ? -1.f : 1.f;
-    const uint32_t flip = buf ? 0u : 0x80000000u;  // of tile t + 1
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      if (s == S - 1) {
-        __syncthreads();
-        read_o(buf ^ 1, 0);
-        read_i(buf ^ 1, 0);
-      }
-      // fragments: the inner ones during the first row, the next outer one in the middle of a row
-      if (s + 1 < NI) read_i(buf, s + 1);
-      if (s % NI == NI - 2 && s / NI + 1 < NO) read_o(buf, s / NI + 1);
-      multiply(s);
-      if (s > 0) flush(s - 1, sign);
-      else flush(S - 1, -sign);  // the last block of the tile before
-      if (s < S - 1) {
-#pragma unroll
-        for (int q = 0; q < L::PIECES; ++q)
-          if (q * (S - 1) / L::PIECES == s) {
-            ld.template stage_piece<FLIP>(q, at, cut, flip);
-            if (ld.frees(q)) ld.load_unit(ld.unit_of(q), off, stride);
-          }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  auto loop = [&](auto flip_tag, auto& ld, __bf16* lds, const uint32_t* stride) {
-    if (kb >= ke) return;
-    typedef std::remove_reference_t<decltype(ld)> L;
-    ld.load(kb, g.K, g.kl, stride);
-#pragma unroll
-    for (int q = 0; q < L::PIECES; ++q) ld.template stage_piece<false>(q, ld.at(lds), kb + ld.k0 >= ke, 0u);
-    ld.load(kb + BK, g.K, g.kl, stride);
-    __syncthreads();
-    read_o(0, 0);
-    read_i(0, 0);
-    int64_t kt = kb;
-    int buf = 0;
-    for (; kt + 2 * BK < ke; kt += BK, buf ^= 1) tile(std::false_type{}, flip_tag, ld, kt, buf, lds, stride);
-    for (; kt < ke; kt += BK, buf ^= 1) tile(std::true_type{}, flip_tag, ld, kt, buf, lds, stride);
-    flush(S - 1, buf ? 1.f : -1.f);
-  };
-  const float* A = static_cast<const float*>(g.A[grp]);
-  const float* B = static_cast<const float*>(g.B[grp]);
-  // waves 0 and 1 stage A, waves 2 and 3 stage B (a wave-uniform choice)
-  if (wave < 2) {
-    SplitLoader<AKF, BM, NKL, NP> ld;
-    ld.init(A, g.a_m, m0, tid & 127);
-    loop(std::integral_constant<bool, (BM <= BN)>{}, ld, As[0], g.kl.sa);
-  } else {
-    SplitLoader<BKF, BN, NKL, NP> ld;
-    ld.init(B, g.b_n, n0, tid & 127);
-    loop(std::integral_constant<bool, (BM > BN)>{}, ld, Bs[0], g.kl.sb);
-  }
-
-  // epilogue (acc[i] -> row 8 (i / 4) + 4 (lane / 32) + i % 4, column lane % 32)
-  if constexpr (NP == 3) {
-    bool nan = false;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) nan |= acc[i][j][r] != acc[i][j][r];
-    if (__any(nan)) {
-      plain_wave_tile<NKL>(g, grp, m0 + wm, n0 + wn, WM, WN, kb, ke, lane);
-      return;
-    }
-  }
-  auto row_of = [&](int i, int r) { return m0 + wm + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
-  auto col_of = [&](int j) { return n0 + wn + j * 32 + (lane & 31); };
-  if (g.split) {
-    float* P = static_cast<float*>(g.partial[grp]) + (int64_t)blockIdx.z * g.M * g.N;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t row = row_of(i, r), col = col_of(j);
-          if (row < g.M && col < g.N) P[row * g.N + col] = acc[i][j][r];
-        }
-    return;
-  }
-  float* __restrict__ C = static_cast<float*>(g.C[grp]);
-  const float alpha = float(g.alpha), beta = float(g.beta);
-  int64_t cn[FN];
-  bool cv[FN];
-#pragma unroll
-  for (int j = 0; j < FN; ++j) {
-    cn[j] = g.c_n[col_of(j)];
-    cv[j] = col_of(j) < g.N;
-  }
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    int64_t cm[16];
-    bool rv[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      cm[r] = g.c_m[row_of(i, r)];
-      rv[r] = row_of(i, r) < g.M;
-    }
-    if (g.beta != 0.0) {
-      // per block, all reads of C first, unconditionally (padded table entries address element 0 of a valid row or
-      // column), so they are in flight together; then the masked read-modify-write stores
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        float cold[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) cold[r] = C[cm[r] + cn[j]];
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (cv[j] && rv[r]) C[cm[r] + cn[j]] = alpha * acc[i][j][r] + beta * cold[r];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (cv[j] && rv[r]) C[cm[r] + cn[j]] = alpha * acc[i][j][r];
-    }
-  }
-}
-
-template <int BM, int BN, int NKL, int NP>
-void launch_k(const GettArgs& a, dim3 grid, hipStream_t s, bool akf, bool bkf) {
-  const dim3 block(256);
-  if (akf && bkf) hipLaunchKernelGGL((gett_split_kernel<BM, BN, true, true, NKL, NP>), grid, block, 0, s, a);
-  else if (akf) hipLaunchKernelGGL((gett_split_kernel<BM, BN, true, false, NKL, NP>), grid, block, 0, s, a);
-  else if (bkf) hipLaunchKernelGGL((gett_split_kernel<BM, BN, false, true, NKL, NP>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gett_split_kernel<BM, BN, false, false, NKL, NP>), grid, block, 0, s, a);
-}
-
-template <int BM, int BN>
-void launch_tile(const GettArgs& a, int groups, int splits, hipStream_t s, bool akf, bool bkf, int planes) {
-  const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  const dim3 grid((unsigned)tiles, (unsigned)groups, (unsigned)splits);
-  if (planes == 3) {
-    constexpr int NP = BM + BN < 384 ? 3 : 2;  // no 192 x 192 tile of three planes: checked by the caller
-    if (a.kl.n <= 2) launch_k<BM, BN, 2, NP>(a, grid, s, akf, bkf);
-    else launch_k<BM, BN, 4, NP>(a, grid, s, akf, bkf);
-  } else {
-    if (a.kl.n <= 2) launch_k<BM, BN, 2, 2>(a, grid, s, akf, bkf);
-    else launch_k<BM, BN, 4, 2>(a, grid, s, akf, bkf);
-  }
-}
-
-}  // namespace
-
 void launch_gett_split(const GettArgs& a, int groups, int splits, hipStream_t s, bool akf, bool bkf, int bm, int bn,
-                       int planes) {
-  if (bm == 192 && bn == 192 && planes == 2) launch_tile<192, 192>(a, groups, splits, s, akf, bkf, 2);
-  else if (bm == 128 && bn == 192) launch_tile<128, 192>(a, groups, splits, s, akf, bkf, planes);
-  else if (bm == 192 && bn == 128) launch_tile<192, 128>(a, groups, splits, s, akf, bkf, planes);
-  else if (bm == 128 && bn == 128) launch_tile<128, 128>(a, groups, splits, s, akf, bkf, planes);
-  else throw Error(MERA_EINVAL, "gett: no split kernel of this tile");
+     int planes) {
+  launch_split<true>(a, groups, splits, s, akf, bkf, bm, bn, planes);
 }
 
 }  // namespace mera
