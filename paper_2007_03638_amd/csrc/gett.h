@@ -61,8 +61,9 @@ struct GettLaunch {
   bool prepare_only = false;  // size the split-K scratch and return without launching
 };
 
-// Chooses tile shape and split-K and launches on ctx.stream; `ctx` provides the split-K scratch. The choice
-// depends only on the tables' extents and the precision, never on `groups`.
+// Chooses kernel, tile shape and split-K and launches on ctx.stream; `ctx` provides the split-K scratch. What fixes a
+// set's result, bit by bit, depends only on the tables (extents and layouts) and the precision, never on `groups` or on
+// where the tensors lie; the alignment of the bases (of all sets) decides how elements are loaded.
 void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l);
 
 }  // namespace mera

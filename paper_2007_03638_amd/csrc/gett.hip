@@ -635,14 +635,17 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   a.beta = l.beta;
   a.split = 0;
 
-  // vector tile loads when both operands' layouts allow them (planned) and every base is 16-byte aligned
+  // Kernel, tile, order of the k's and split-K follow from what the layouts allow (planned); where the bases lie only decides
+  // whether vectors are loaded whole or by elements, for all sets of the launch. An operand set thus gets the same bits
+  // wherever its tensors lie and whatever else is in the group.
   const int vw = l.prec == Prec::F64 ? 2 : 4;
-  bool a16 = t.a_vw >= vw, b16 = t.b_vw >= vw;
+  const bool a_vec = t.a_vw >= vw, b_vec = t.b_vw >= vw;
+  bool a16 = a_vec, b16 = b_vec;  // 16-byte loads: the layout allows them and every base is aligned
   for (int g = 0; g < G; ++g) {
     a16 = a16 && (uintptr_t)l.A[g] % 16 == 0;
     b16 = b16 && (uintptr_t)l.B[g] % 16 == 0;
   }
-  bool vec = a16 && b16;
+  bool plan_vec = a_vec && b_vec;  // tile loads move vectors when both operands allow it
   // FP32 operands with extents of 128 and more run on the bf16 matrix cores from split operands: three planes for the
   // FP32 form (chi^9 steps at chi = 24: 172 TFLOP/s against 127 on the FP32 instructions), two for the split-bf16 form.
   // Below 128 rows or columns a launch is bound by latency and the FP32 tiles stay. Below kSplitMinK a step is bound by
@@ -654,25 +657,26 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
   const bool split_form = t.M >= 128 && t.N >= 128 &&
                           (l.prec == Prec::BF16X3 || (l.prec == Prec::F32 && t.K >= kSplitMinK));
   const int planes = !split_form ? 0 : l.prec == Prec::F32 ? 3 : 2;
-  if (planes > 0) vec = vec && t.kl.n >= 1 && t.kl.ext[0] % 2 == 0;
-  else if (l.prec == Prec::BF16X3) vec = false;
+  if (planes > 0) plan_vec = plan_vec && t.kl.n >= 1 && t.kl.ext[0] % 2 == 0;
+  else if (l.prec == Prec::BF16X3) plan_vec = false;
+  const bool vec = plan_vec && a16 && b16;
 
-  Tile tile = choose_tile(l.prec, t.M, t.N, planes, planes == 3 && !vec && (t.a_kfast || t.b_kfast));
+  Tile tile = choose_tile(l.prec, t.M, t.N, planes, planes == 3 && !plan_vec && (t.a_kfast || t.b_kfast));
   // Small launches: 32 x 32 tiles straight from global memory (gett_direct.hip) where the LDS tiles would leave half of
   // the 256 CUs idle and the work is small. Over the 500 contractions of the binary and ternary programs at chi = 4 .. 20
   // this line is 30 % faster on the (geometric) average than the LDS tiles with their best split, 3 % short of the better
   // kernel each time. Beyond it the LDS tiles' reuse wins: FP64 10000 x 100 x 100 (158 tiles) 19.6 / 20.8 us LDS / direct,
   // 20736 x 144 x 144 (486 tiles) 34 / 49 us; this side of it 144 x 144 x 20736 (6 tiles) 73 / 49 us, FP32
   // 20 x 8000 x 8000 (63 tiles) 117 / 78 us. Where each k is loaded by itself (the fastest contracted leg no multiple
-  // of 4, or a k-walking operand without 16-byte loads) the line lies lower: FP64 81 x 729 x 6561 (0.77 GFLOP) 44 / 74 us,
-  // 121 x 121 x 14641 (0.43) 47 / 26 us. Large FP32 outputs from few k's stay with the LDS tiles, which write whole
+  // of 4, or a k-walking operand whose layout allows no 16-byte loads) the line lies lower: FP64 81 x 729 x 6561
+  // (0.77 GFLOP) 44 / 74 us, 121 x 121 x 14641 (0.43) 47 / 26 us. Large FP32 outputs from few k's stay with the LDS tiles, which write whole
   // lines (4096 x 4096 x 16 25 / 59 us); by time alone that line would lie at 4 million elements (1728 x 1728 x 12
   // 17 / 13 us, 1728 x 144 x 12 15 / 5 us), but the tests of the chi = 12 evaluation ask for the 192 x 192 tile, whose
   // launches there have 250 thousand.
-  const bool k4 = t.kl.n >= 1 && t.kl.ext[0] % 4 == 0 && (a16 || !t.a_kfast) && (b16 || !t.b_kfast);
+  const bool k4 = t.kl.n >= 1 && t.kl.ext[0] % 4 == 0 && (a_vec || !t.a_kfast) && (b_vec || !t.b_kfast);
   const bool direct = 2.0 * (double)t.M * (double)t.N * (double)t.K < (k4 ? 3e9 : 5e8) &&
                       ((t.M + tile.bm - 1) / tile.bm) * ((t.N + tile.bn - 1) / tile.bn) < 128 &&
-                      !(l.prec == Prec::F32 && vec && t.M >= 128 && t.N >= 128 && t.K < kSplitMinK && t.M * t.N >= 200000);
+                      !(l.prec == Prec::F32 && plan_vec && t.M >= 128 && t.N >= 128 && t.K < kSplitMinK && t.M * t.N >= 200000);
   if (direct) tile = Tile{kDirectTile, kDirectTile};
   const int BMsel = tile.bm, BNsel = tile.bn;
   // the m and n offset tables are padded to multiples of 128; every tile must lie within them
@@ -718,11 +722,13 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
     a.split = 1;
   }
   if (l.prepare_only) return;
+  // the split kernels of three planes walk k without 16-byte loads in 128 x 128 tiles only: same sums, smaller tiles
+  if (planes == 3 && !direct && !vec && (t.a_kfast || t.b_kfast)) tile = Tile{128, 128};
   hipStream_t s = ctx.stream;
   LaunchRecord rec;
   if (ctx.profiling) {
     rec.kernel = std::string("gett<") + (l.prec == Prec::F64 ? "f64" : (l.prec == Prec::F32 ? "f32" : "bf16x3")) +
-                 "," + std::to_string(BMsel) + "x" + std::to_string(BNsel) + (t.a_kfast ? ",Ak" : ",Am") +
+                 "," + std::to_string(tile.bm) + "x" + std::to_string(tile.bn) + (t.a_kfast ? ",Ak" : ",Am") +
                  (t.b_kfast ? ",Bk" : ",Bn") + (direct ? ",d" : vec ? ",v" : "") + (t.kl.n <= 2 ? ",k2" : ",k4") +
                  (direct ? "" : planes == 3 ? ",s3" : planes == 2 ? ",s2" : "") +
                  (splits > 1 ? ",splitk" : "") + (G > 1 ? ",grouped" : "") + ">";
@@ -732,13 +738,13 @@ void gett_run(Ctx& ctx, const GettTables& t, const GettLaunch& l) {
     rec.stop = ctx.take_event();
     MERA_HIP(hipEventRecord(rec.start, s));
   }
-  const int sel = BMsel * 1000 + BNsel;
+  const int sel = tile.bm * 1000 + tile.bn;
   const bool akf = t.a_kfast, bkf = t.b_kfast;
 
   if (direct) {
-    launch_gett_direct(a, G, splits, s, l.prec, waves, akf && a16, bkf && b16);
+    launch_gett_direct(a, G, splits, s, l.prec, waves, (akf && a_vec) || (bkf && b_vec), akf && a16, bkf && b16);
   } else if (planes > 0) {
-    (vec ? launch_gett_split : launch_gett_split_scalar)(a, G, splits, s, akf, bkf, BMsel, BNsel, planes);
+    (vec ? launch_gett_split : launch_gett_split_scalar)(a, G, splits, s, akf, bkf, tile.bm, tile.bn, planes);
   } else if (l.prec == Prec::F64) {
     if (sel == 128064) launch_tile<double, 128, 64, 16>(a, G, splits, s, akf, bkf, vec);
     else launch_tile<double, 64, 64, 16>(a, G, splits, s, akf, bkf, vec);

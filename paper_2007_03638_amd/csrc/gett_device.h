@@ -73,10 +73,11 @@ void launch_gett_split_scalar(const GettArgs& a, int groups, int splits, hipStre
                               int bn, int planes);
 
 // Contraction in 32 x 32 tiles read straight from global memory, for launches too small to fill the chip with LDS tiles
-// (gett_direct.hip); any layout and alignment. av, bv: the operand's unit-stride leg is a contracted one and it may be
-// read in 16-byte loads.
+// (gett_direct.hip); any layout and alignment. quads: the layout of an operand whose unit-stride leg is a contracted one
+// allows 16-byte loads, so the k's are taken in quadruples (this fixes the order of the sums); av, bv: such an operand's
+// bases are aligned too, so that it is read that way.
 constexpr int kDirectTile = 32, kDirectChunk = 16;
-void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, Prec prec, int waves, bool av,
-                        bool bv);
+void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, Prec prec, int waves, bool quads,
+                        bool av, bool bv);
 
 }  // namespace mera

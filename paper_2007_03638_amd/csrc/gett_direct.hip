@@ -64,12 +64,14 @@ __device__ inline T operand(T x) {
   return x;
 }
 
-// AV, BV: the operand's unit-stride leg is the fastest contracted one, its extent a multiple of 4, and its addresses are
-// 16-byte aligned, so that four consecutive k's are read at once.
+// QUADS: the fastest contracted leg's extent is a multiple of 4, and a lane takes four consecutive k's of a chunk (chosen
+// from the layouts). AV, BV (only with QUADS): that leg is the operand's unit-stride leg and its addresses are 16-byte
+// aligned, so that the four are read at once (chosen from the addresses too; the sums are the same either way).
 // SPLIT: the split-bf16 form; each operand element is replaced by the sum of the two bf16 numbers it is split into.
-template <typename T, int NKL, int WAVES, bool AV, bool BV, bool SPLIT>
+template <typename T, int NKL, int WAVES, bool QUADS, bool AV, bool BV, bool SPLIT>
 __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
   using F = Mma16<T>;
+  static_assert(QUADS || !(AV || BV), "vectors of four k's");
   __shared__ T red[WAVES][TILE][TILE + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t tn = (g.N + TILE - 1) / TILE;
@@ -108,13 +110,12 @@ __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = T(0);
 
-  // Matrix instruction s of a chunk takes the k's 4 s + kq, in ascending order. With vector loads lane group kq takes
-  // 4 kq + s instead: the order is free as long as both operands follow it, and a row's four k's are one load.
+  // Matrix instruction s of a chunk takes the k's 4 s + kq, in ascending order. With QUADS lane group kq takes
+  // 4 kq + s instead: the order is free as long as both operands follow it, and a row's four k's can be one load.
   static_assert(CHUNK == 16, "four lane groups of four k's");
-  constexpr bool V = AV || BV;
   T av[2][2][4], bv[2][2][4];  // two chunks: one multiplied, the next one on its way
   auto load = [&](int slot, int64_t k) {
-    if constexpr (V) {  // ke is a multiple of 4 then
+    if constexpr (QUADS) {  // ke is a multiple of 4 then
       const uint32_t kc = (uint32_t)(k + 4 * kq < ke ? k + 4 * kq : ke - 4);
       const uint64_t oa = k_offset<NKL>(kc, g.kl, g.kl.sa), ob = k_offset<NKL>(kc, g.kl, g.kl.sb);
 #pragma unroll
@@ -138,7 +139,7 @@ __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
   auto mul = [&](int slot, int64_t k) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const bool in = k + (V ? 4 * kq + s : 4 * s + kq) < ke;
+      const bool in = k + (QUADS ? 4 * kq + s : 4 * s + kq) < ke;
       T x[2], y[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -183,36 +184,38 @@ __global__ void __launch_bounds__(64 * WAVES) gett_direct_kernel(GettArgs g) {
 }
 
 template <typename T, int NKL, int WAVES, bool SPLIT>
-void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, bool av, bool bv) {
+void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, bool quads, bool av, bool bv) {
   const dim3 block(64 * WAVES);
-  if (av && bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, true, SPLIT>), grid, block, 0, s, a);
-  else if (av) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, false, SPLIT>), grid, block, 0, s, a);
-  else if (bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, false, true, SPLIT>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, false, false, SPLIT>), grid, block, 0, s, a);
+  if (!quads) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, false, false, false, SPLIT>), grid, block, 0, s, a);
+  else if (av && bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, true, true, SPLIT>), grid, block, 0, s, a);
+  else if (av) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, true, false, SPLIT>), grid, block, 0, s, a);
+  else if (bv) hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, false, true, SPLIT>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gett_direct_kernel<T, NKL, WAVES, true, false, false, SPLIT>), grid, block, 0, s, a);
 }
 
 template <typename T, bool SPLIT>
-void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, int waves, bool av, bool bv) {
+void launch_direct(const GettArgs& a, dim3 grid, hipStream_t s, int waves, bool quads, bool av, bool bv) {
   if (waves == 8) {
-    if (a.kl.n <= 2) launch_direct<T, 2, 8, SPLIT>(a, grid, s, av, bv);
-    else launch_direct<T, 4, 8, SPLIT>(a, grid, s, av, bv);
+    if (a.kl.n <= 2) launch_direct<T, 2, 8, SPLIT>(a, grid, s, quads, av, bv);
+    else launch_direct<T, 4, 8, SPLIT>(a, grid, s, quads, av, bv);
   } else {
-    if (a.kl.n <= 2) launch_direct<T, 2, 4, SPLIT>(a, grid, s, av, bv);
-    else launch_direct<T, 4, 4, SPLIT>(a, grid, s, av, bv);
+    if (a.kl.n <= 2) launch_direct<T, 2, 4, SPLIT>(a, grid, s, quads, av, bv);
+    else launch_direct<T, 4, 4, SPLIT>(a, grid, s, quads, av, bv);
   }
 }
 
 }  // namespace
 
-void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, Prec prec, int waves, bool av, bool bv) {
+void launch_gett_direct(const GettArgs& a, int groups, int splits, hipStream_t s, Prec prec, int waves, bool quads,
+                        bool av, bool bv) {
   const int64_t tiles = ((a.M + TILE - 1) / TILE) * ((a.N + TILE - 1) / TILE);
   const dim3 grid((unsigned)tiles, (unsigned)groups, (unsigned)splits);
-  const bool k4 = a.kl.n >= 1 && a.kl.ext[0] % 4 == 0;
-  av = av && k4;
-  bv = bv && k4;
-  if (prec == Prec::F64) launch_direct<double, false>(a, grid, s, waves, av, bv);
-  else if (prec == Prec::F32) launch_direct<float, false>(a, grid, s, waves, av, bv);
-  else launch_direct<float, true>(a, grid, s, waves, av, bv);
+  quads = quads && a.kl.n >= 1 && a.kl.ext[0] % 4 == 0;
+  av = av && quads;
+  bv = bv && quads;
+  if (prec == Prec::F64) launch_direct<double, false>(a, grid, s, waves, quads, av, bv);
+  else if (prec == Prec::F32) launch_direct<float, false>(a, grid, s, waves, quads, av, bv);
+  else launch_direct<float, true>(a, grid, s, waves, quads, av, bv);
 }
 
 }  // namespace mera
