@@ -578,11 +578,11 @@ int64_t rup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // sums and fragments do not fit the registers (spilling, it ran 159 TFLOP/s against 171 with 128 x 192), and with
 // 128 x 128 only (`only128`) where an operand is walked along k without 16-byte loads. A 192-row (column) tile is only
 // chosen when it pads no more than a 128-row one, so the offset tables, padded to multiples of 128, cover every tile.
-// Split-bf16 with 64-wide tiles: scalar loads. 64-wide tiles for extents below 128.
+// 64-wide tiles for extents below 128 (split-bf16: scalar loads).
 Tile choose_tile(Prec p, int64_t M, int64_t N, int planes, bool only128) {
   const bool bigm = M >= 128, bign = N >= 128;
   if (p == Prec::F64) return Tile{bigm ? 128 : 64, 64};
-  if ((p == Prec::BF16X3 && planes == 0) || !bigm || !bign || only128) return Tile{bigm ? 128 : 64, bign ? 128 : 64};
+  if (!bigm || !bign || only128) return Tile{bigm ? 128 : 64, bign ? 128 : 64};
   const Tile cand[4] = {{192, 192}, {128, 192}, {192, 128}, {128, 128}};
   Tile best = cand[3];
   double best_pad = 1e300;

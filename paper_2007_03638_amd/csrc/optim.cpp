@@ -451,8 +451,8 @@ void Metric::compute(Ctx& ctx, const std::vector<MatView>& rho) {
   g.resize(k);
   warm.resize(k, 0);
   p.assign(k, 0);
-  // every factor's matrix is prepared first (each in its own scratch), then all are decomposed together: the
-  // small ones (p <= 64) in one launch, one workgroup each
+  // every factor's matrix is prepared first (each in its own scratch), then all are decomposed together: those of up to
+  // 200 rows side by side, one workgroup each
   std::vector<JacobiTask> tasks;
   tasks.reserve(k);
   std::vector<std::pair<size_t, double*>> rotate;  // warm-started factors and their symmetrised rho

@@ -54,7 +54,8 @@ void multi_axpby_dev(Ctx& ctx, const VPtr* v, const double* c_dev, double s, int
 void normalize_dev(Ctx& ctx, VPtr x, int64_t n, double* nrm_dev, double* work_dev);
 
 // Symmetric eigendecomposition of a dim x dim FP64 matrix (row-major, device) by cyclic two-sided Jacobi
-// rotations in tournament order: A = V diag(lam) V^T, eigenvectors in the columns of V. `a` is overwritten.
+// rotations in tournament order: A = V diag(lam) V^T, eigenvectors in the columns of V. `a` is left undefined (it is
+// read only up to 200 rows, and overwritten with the rotated matrix above).
 // v_init: v holds an orthogonal basis Q on entry and a = Q^T A Q; the rotations are then accumulated onto Q, so
 // that v returns the eigenvectors of A (few sweeps when Q nearly diagonalises A). Matrices up to 200 x 200 run in two
 // launches (the sweeps on A in LDS by one workgroup, then the recorded rotations on V); larger ones launch one kernel

@@ -372,6 +372,12 @@ struct JacobiDevBatch {
 // Rotation that zeroes the off-diagonal entry of a pair (Golub & Van Loan's symmetric Schur step). The angle comes from
 // the hardware's reciprocal and square-root estimates (about 1e-7: the rotated entry is computed, not set to zero,
 // and shrinks by that factor), c = (1 + t^2)^{-1/2} is refined by two Newton steps, so that c^2 + s^2 = 1 to rounding.
+// An inexact angle only leaves a later sweep something to rotate; what the result keeps is how orthogonal each rotation
+// is, and the refined c is nearer to that than 1 / sqrt(1 + t^2). Error of the preconditioner against FP64 eigh over 20
+// sizes from 2 to 200, six kinds of spectra and delta = 0.02 and 1e-4, geometric means of the kinds and largest:
+// 3e-15 .. 6e-14 and 2.8e-12; with the division and square root of FP64 in this place 7e-15 .. 7e-14 and 9e-13, and on
+// the per-round kernels, which have those, 7e-15 .. 8e-14 and 1.6e-10. Three cold 144 x 144 decompositions 2.8 ms, with
+// division and square root 3.1.
 __device__ inline double2 jacobi_rotation(double aii, double aij, double ajj) {
   if (!(fabs(aij) > 0x1p-1000) && aij == aij) return double2{1.0, 0.0};
   const double tau = (ajj - aii) * __builtin_amdgcn_rcp(2.0 * aij);
