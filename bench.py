@@ -122,21 +122,29 @@ def cpu_baseline(a, sample_chi, sample_T, flops_sample, flops_bench):
                               f"{flops_bench:.3e} at chi={a.chi})")
 
 
-def counter_traffic(kernel_variant):
+def counter_traffic(kernel_variant, algorithmic_bytes=None):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter summaries, or None when the
-    kernel's source changed since the counters were taken or no summary covers the variant."""
+    kernel's source or the tile order it shares with the others (gett_device.h) changed since the counters were taken, no
+    summary covers the variant, or the launches counted were of another size (algorithmic bytes more than a tenth off)."""
     import hashlib
+
+    def sha(source):
+        return hashlib.sha256(open(os.path.join(ROOT, "paper_2007_03638_amd", "csrc", source), "rb").read()).hexdigest()[:16]
     for summary, source in (("gett_f32_chi24_counters.md", "gett.hip"), ("gett_split_chi24_counters.md", "gett_split_device.h")):
         path = os.path.join(ROOT, "profiles", summary)
-        src = os.path.join(ROOT, "paper_2007_03638_amd", "csrc", source)
         if not os.path.exists(path):
             continue
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
         fields = dict(l.split(": ", 1) for l in open(path).read().splitlines() if ": " in l and not l.startswith("|"))
-        if fields.get("gett_source_sha256_prefix", "").strip() != sha:
+        if fields.get("gett_source_sha256_prefix", "").strip() != sha(source):
             continue
-        if fields.get("kernel_variant", "").strip() == kernel_variant:
-            return float(fields["traffic_bytes_per_launch"])
+        if fields.get("gett_device_sha256_prefix", "").strip() != sha("gett_device.h"):
+            continue
+        if fields.get("kernel_variant", "").strip() != kernel_variant:
+            continue
+        if algorithmic_bytes is not None and \
+                abs(algorithmic_bytes - float(fields["algorithmic_bytes_per_launch"])) > 0.1 * algorithmic_bytes:
+            continue
+        return float(fields["traffic_bytes_per_launch"])
     return None
 
 
@@ -257,7 +265,7 @@ def run_eval_bench(a):
         "gnorm": state["gnorm"],
         "contraction_time_fraction": gemm_time / dt,
         "roofline": {"bound": "mfma", "kernel": top["kernel"], "achieved": achieved, "peak": peak,
-                     "unit": "TFLOP/s", "frac": achieved / peak, "traffic": counter_traffic(top["kernel"]),
+                     "unit": "TFLOP/s", "frac": achieved / peak, "traffic": counter_traffic(top["kernel"], top["bytes"] / top["launches"]),
                      "algorithmic_bytes": top["bytes"] / top["launches"],
                      "launches": top["launches"], "avg_launch_ms": 1000.0 * top["seconds"] / top["launches"]},
         "krylov_applications_per_eval": (state["krylov_applications"] - s0.get("krylov_applications", 0)) / max(evals, 1),
