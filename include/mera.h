@@ -47,8 +47,8 @@ typedef enum {
  * operands and accumulation, double-precision dot products, traces and Krylov scalars; large contractions run on the
  * bf16 MFMA units with each operand split into three bf16 parts (24 mantissa bits at every magnitude) and the six leading
  * products of the parts, whose error against FP64 is below that of the single-precision MFMA; a result that this form
- * cannot give (a non-finite operand element, one above 2^112, a sum above 2^96) is formed from unscaled parts or by
- * single-precision multiply-adds, element by element.
+ * cannot give (a non-finite operand element, one above 2^112, a sum above 2^96) is formed from unscaled parts or on the
+ * single-precision MFMA, element by element.
  * BF16X3: each FP32 operand split into bf16 hi + lo parts, products hi*hi + hi*lo + lo*hi on the bf16
  * MFMA units with FP32 accumulation. */
 typedef enum { MERA_FP64 = 0, MERA_FP32 = 1, MERA_BF16X3 = 2 } mera_prec;

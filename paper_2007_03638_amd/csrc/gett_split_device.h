@@ -22,7 +22,7 @@
 // What bounds it: the bf16 matrix cores and the power they draw. 2.5 PFLOP/s / 6 = 417 TFLOP/s of contraction
 // arithmetic in the FP32 form against 157 TFLOP/s on the FP32 matrix instructions; 833 in the split-bf16 form. At full
 // load the card lowers its clock (1.7 GHz measured on the chi^9 steps at chi = 24, where the matrix cores are busy
-// 0.57-0.64 of the time): a large bf16 library product reaches 1405 TFLOP/s on it, i.e. 234 and 468 per plane product. Measured: FP32 form 172
+// 0.57-0.64 of the time): a large bf16 library product reaches 1405 TFLOP/s on it, i.e. 234 and 468 per plane product. Measured: FP32 form 167-179
 // TFLOP/s with 128 x 192 tiles (127 before, on the FP32 instructions with 192 x 192), split-bf16 form 310-322 with
 // 192 x 192 tiles (221 before with 128 x 128 tiles and one barrier per 32 k's).
 //
@@ -215,47 +215,40 @@ struct SplitLoader {
   static constexpr int unit_of(int q) { return KF ? q : q >> 1; }
 };
 
-// Element (row, col) by FP32 multiply-adds over k.
+// Elements of one wave's 32 x 32 block whose scaled sums were not finite (bit r of `todo`: register r of this lane), again
+// from operands read straight from global memory: first the same products and sums without the scale. Of these, the
+// elements that are no number (an infinite element, or one that bf16 rounds to infinity, splits into inf - inf, where FP32
+// arithmetic may give an infinity or a number) or are below 2^60, in which an element that lost low bits may count (the
+// loss is below 2^-134 times the other operand's element, together below 2^26 for K < 2^31), on the FP32 matrix
+// instructions. One block at a time, which leaves the main loop its registers. An ascending map at chi = 16 whose operator
+// lies beyond the scale's range takes 16 ms this way (ordinarily 4.5), one with a NaN in it 25 (by multiply-adds for each
+// element 104); ternary at chi = 16 2.0 and 2.2 ms (0.67; 20).
 template <int NKL>
-__device__ inline float plain_element(const GettArgs& g, int grp, int64_t row, int64_t col, int64_t kb, int64_t ke) {
-  const float* a = static_cast<const float*>(g.A[grp]) + g.a_m[row];
-  const float* b = static_cast<const float*>(g.B[grp]) + g.b_n[col];
-  float s = 0.f;
-  for (int64_t k = kb; k < ke && s == s; ++k)
-    s = fmaf(a[k_offset<NKL>((uint32_t)k, g.kl, g.kl.sa)], b[k_offset<NKL>((uint32_t)k, g.kl, g.kl.sb)], s);
-  return s;
-}
-
-// Elements of one wave's 32 x 32 block whose scaled sums were not finite (bit r of `todo`: register r of this lane): the
-// same products and sums without the scale, from operands read straight from global memory. Of these, the elements one by
-// one that are no number (an infinite element, or one that bf16 rounds to infinity, splits into inf - inf, where FP32
-// arithmetic may give an infinity or a number) or below 2^60, in which an element that lost low bits may count (the loss
-// is below 2^-134 times the other operand's element, together below 2^26 for K < 2^31).
-template <int NKL>
-__device__ inline void redo_block(const GettArgs& g, int grp, int64_t r0, int64_t c0, int64_t kb, int64_t ke, int lane,
+__device__ inline void redo_block(const GettArgs& g, int grp, int64_t r0, int64_t c0, uint32_t kb, uint32_t ke, int lane,
                                   uint32_t todo) {
   // rows and columns past the extents read padded table entries (offset 0)
   const float* a = static_cast<const float*>(g.A[grp]) + g.a_m[r0 + (lane & 31)];
   const float* b = static_cast<const float*>(g.B[grp]) + g.b_n[c0 + (lane & 31)];
+  auto load = [&](uint32_t k, float& x, float& y) {
+    const bool in = k < ke;
+    const uint32_t kc = in ? k : ke - 1;
+    x = a[k_offset<NKL>(kc, g.kl, g.kl.sa)];
+    y = b[k_offset<NKL>(kc, g.kl, g.kl.sb)];
+    if (!in) x = y = 0.f;
+  };
   f32x16 acc{};
   float sign = 1.f;
-#pragma nounroll
-  for (int64_t kt = kb; kt < ke; kt += BK, sign = -sign) {
+#pragma unroll 2
+  for (uint32_t kt = kb; kt < ke; kt += BK, sign = -sign) {
     uint32_t pa[3][4], pb[3][4];
+    float x[8], y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) load(kt + 8 * (lane >> 5) + e, x[e], y[e]);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float x[2], y[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int64_t k = kt + 8 * (lane >> 5) + 2 * j + e;
-        const bool in = k < ke;
-        const uint32_t kc = (uint32_t)(in ? k : ke - 1);
-        x[e] = in ? sign * a[k_offset<NKL>(kc, g.kl, g.kl.sa)] : 0.f;
-        y[e] = in ? b[k_offset<NKL>(kc, g.kl, g.kl.sb)] : 0.f;
-      }
       uint32_t u[3], v[3];
-      split_pair<3>(x[0], x[1], u);
-      split_pair<3>(y[0], y[1], v);
+      split_pair<3>(sign * x[2 * j], sign * x[2 * j + 1], u);
+      split_pair<3>(y[2 * j], y[2 * j + 1], v);
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
         pa[p][j] = u[p];
@@ -269,11 +262,26 @@ __device__ inline void redo_block(const GettArgs& g, int grp, int64_t r0, int64_
       t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(pa[plane_a<3>(q)]), frag(pb[plane_b<3>(q)]), t, 0, 0, 0);
     acc += sign * t;
   }
+  f32x16 plain{};
+  uint32_t rest = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) rest |= fabsf(acc[r]) >= 0x1p60f ? 0u : 1u << r;
+  rest &= todo;
+  if (__any(rest != 0)) {
+#pragma nounroll
+    for (uint32_t kt = kb; kt < ke; kt += BK) {
+      float x[BK / 2], y[BK / 2];
+#pragma unroll
+      for (int s = 0; s < BK / 2; ++s) load(kt + 2 * s + (lane >> 5), x[s], y[s]);
+#pragma unroll
+      for (int s = 0; s < BK / 2; ++s) plain = __builtin_amdgcn_mfma_f32_32x32x2f32(x[s], y[s], plain, 0, 0, 0);
+    }
+  }
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int64_t row = r0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), col = c0 + (lane & 31);
     if (!((todo >> r) & 1) || row >= g.M || col >= g.N) continue;
-    const float s = fabsf(acc[r]) >= 0x1p60f ? acc[r] : plain_element<NKL>(g, grp, row, col, kb, ke);
+    const float s = (rest >> r) & 1 ? plain[r] : acc[r];
     if (g.split) {
       (static_cast<float*>(g.partial[grp]) + (int64_t)blockIdx.z * g.M * g.N)[row * g.N + col] = s;
     } else {

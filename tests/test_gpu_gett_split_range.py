@@ -62,3 +62,31 @@ def test_small_operands_scale_exactly(ctx, chi, scale):
     kw = dict(prec="fp32", d=chi, geometry="ternary")
     A, B = ctx.ascend(1, chi, 1, u, w, h, **kw), ctx.ascend(1, chi, 1, u, w, scale * h, **kw)
     assert np.array_equal(scale * to_np(A), to_np(B))
+
+
+@pytest.mark.parametrize("geometry,chi", [("ternary", 16), ("binary", 12)])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_non_finite_operators_take_a_few_passes(ctx, geometry, chi, value):
+    """A NaN or an infinity in h spreads over every result. Bound: the ordinary pass, one with unscaled operands and one on
+    the FP32 matrix instructions (1.4 times as long), the last two with operands that are not staged for the whole tile
+    (three times the loads): 1 + 3 + 3 * 1.4, half as much again for the scatter of short launches."""
+    ter = geometry == "ternary"
+    u, w = inputs.mera_init(320 + chi, [(chi, chi)], 3 if ter else 2)[0]
+    h = inputs.symmetric_operator(321, chi ** (2 if ter else 3))
+    bad = h.copy()
+    bad[3, 3] = value
+
+    def seconds(x):
+        best = np.inf
+        for _ in range(4):
+            ctx.profile(True)
+            A = ctx.ascend(1, chi, 1, u, w, x, prec="fp32", d=chi, geometry=geometry)
+            best = min(best, sum(s["seconds"] for s in ctx.kernel_stats()))
+            ctx.profile(False)
+        return best, to_np(A)
+
+    t, _ = seconds(h)
+    tb, A = seconds(bad)
+    print(f"{geometry} chi={chi} {value}: {1e3 * t:.3f} ms, {1e3 * tb:.3f} ms, {tb / t:.1f} times", flush=True)
+    assert np.all(np.isnan(A))
+    assert tb < 12.3 * t
